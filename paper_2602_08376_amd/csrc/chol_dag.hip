@@ -73,6 +73,7 @@ __device__ bool wait_flag(const int* flag, int* err) {
   for (uint32_t it = 0;; ++it) {
     if (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the invalidation is complete
       return true;
     }
     if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return false;
@@ -89,13 +90,20 @@ __device__ bool wait_flag(const int* flag, int* err) {
 // the waves of a workgroup share the L1), the workgroup meets, then one
 // thread writes the L2 back and sets the flag (an agent-scope release, the
 // mirror of wait_flag, where one thread acquires and a barrier follows).
-// One agent-scope fence per tile instead of one per wave.
+// One agent-scope fence per tile instead of one per wave.  The compiler drops
+// the wait that belongs between the fence's write-back of the L2 and the flag
+// store (it counts no memory operation there), and a reader on another XCD
+// that saw the flag first read parts of a tile from before: at m = 5120 one
+// factor in six was wrong or had a negative pivot.  Hence the explicit wait;
+// on the acquiring side one keeps the barrier that lets the other waves load
+// behind the invalidation.
 __device__ __forceinline__ void stores_done() {
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): loads and stores complete
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
 }
 __device__ __forceinline__ void release_flag(int* flag) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the write-back is complete
   __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void publish(int* flag) {
