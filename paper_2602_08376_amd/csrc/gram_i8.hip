@@ -6,20 +6,24 @@
 // Splitting (the Ozaki scheme: exact products of split operands on integer
 // matrix units).  Every row of X~ and of D = X - X~ (the difference taken
 // exactly in fp64) is scaled by a power of two 2^-e, e the row's exponent in
-// the chunk (max |x| < 2^e), and written as four signed digits,
-//   x = 2^e (a1 2^-6 + a2 2^-13 + a3 2^-20 + a4 2^-27) + r,  |a_p| <= 64,
-// |r| <= 2^(e-28): digit p is the rounded remainder after digit p - 1, so
-// every value is kept to 28 bits below its row's maximum (every fp32 value
-// within 2^-4 of 2^e exactly).  A product of two rows is then
-//   2^(e_i + e_j - 12) sum_w 2^(-7 (w - 2)) sum_{p+q=w} a_p . b_q,
+// the chunk (max |x| <= 2^e 127/128), rounded to 31 bits below 2^e and
+// written as its four balanced bytes,
+//   x = 2^(e-31) (a1 2^24 + a2 2^16 + a3 2^8 + a4) + r,  -128 <= a_p <= 127,
+// |r| <= 2^(e-32) (every fp32 value within 2^-7 of 2^e exactly).  A product
+// of two rows is then
+//   2^(e_i + e_j - 14) sum_w 2^(-8 (w - 2)) sum_{p+q=w} a_p . b_q,
 // whose inner sums are int8 dot products accumulated exactly in int32 by
-// v_mfma_i32_16x16x64_i8.  The digit products with p + q <= 6 are kept
-// (thirteen per tile, in five int32 accumulators, one per w); the dropped
-// ones (p + q >= 7) have random signs and lie below 2^-47 of the row maxima's
-// product.  Stopping at p + q <= 5 would drop a3 . a3 >= 0 on the diagonal,
-// a bias of about 2^-28 of each diagonal entry.  The accumulators are flushed
-// to fp64 once per sub-chunk of at most 32768 tokens
-// (|sum| <= 4 . 64 . 64 . 32768 < 2^31).
+// v_mfma_i32_16x16x64_i8, one int32 accumulator per w.  The ten digit
+// products with p + q <= 5 are kept, and for the Gram a3 . b3 too.  The
+// dropped ones have random signs: the largest, a2 . b4, a4 . b2 and (cross
+// term) a3 . b3, are about 2^-29 of a mean product per token.  In the Gram
+// a3 . b3 is not of random sign on the diagonal or between equal rows, where
+// leaving it out would be a bias.  The matrix cores set this kernel's time,
+// so it goes by the number of products: seven-bit digits need thirteen for
+// three times the error (1024 rows, 32768 tokens, rms relative to
+// sqrt(G_ii G_jj): 4.8e-11; here 1.8e-11 in G, 2.6e-11 in E).  The
+// accumulators are flushed to fp64 once per sub-chunk of at most 32704 tokens
+// (|sum| <= 4 . 128 . 128 . 32704 < 2^31).
 //
 // Layout of the split operands (written by split_kernel): per tensor, digit
 // plane p, 64-token step s and 16-row block b one 1 KB block in the order the
@@ -52,10 +56,18 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 
 // ---- split ------------------------------------------------------------------
 
-// Row exponents of the chunk: eq[i] for X~ rows, ed[i] for D = X - X~ rows,
-// the smallest e with max |x| < 2^e (0 for an all-zero row and for the
-// padding rows up to a whole tile).  One workgroup per row; with `vec` the
-// rows are read 16 bytes per lane.
+// Exponent of a row with largest magnitude mx: the smallest e with
+// mx <= 2^e 127/128, so that the top digit of a value fits a signed byte (0
+// for an all-zero row).
+__device__ __forceinline__ int digit_exponent(double mx) {
+  int e;
+  const double f = frexp(mx, &e);   // mx = f 2^e, f in [0.5, 1)
+  return mx > 0.0 ? (f > 127.0 / 128.0 ? e + 1 : e) : 0;
+}
+
+// Row exponents of the chunk: eq[i] for X~ rows, ed[i] for D = X - X~ rows
+// (0 for the padding rows up to a whole tile).  One workgroup per row; with
+// `vec` the rows are read 16 bytes per lane.
 __global__ __launch_bounds__(256) void row_exponent_kernel(const float* __restrict__ Xq,
                                                            const float* __restrict__ Xr,
                                                            int64_t m, int64_t T, int64_t ldx,
@@ -103,27 +115,29 @@ __global__ __launch_bounds__(256) void row_exponent_kernel(const float* __restri
   if (tid == 0) {
     mq = fmax(fmax(red[0][0], red[0][1]), fmax(red[0][2], red[0][3]));
     md = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
-    int e;
-    (void)frexp(mq, &e);   // mq = f 2^e, f in [0.5, 1): mq < 2^e
-    eq[row] = mq > 0.0 ? e : 0;
-    (void)frexp(md, &e);
-    ed[row] = md > 0.0 ? e : 0;
+    eq[row] = digit_exponent(mq);
+    ed[row] = digit_exponent(md);
   }
 }
 
-// Four digits of y in (-1, 1): y = a1 2^-6 + a2 2^-13 + a3 2^-20 + a4 2^-27 + r.
-__device__ __forceinline__ void split4(double y, int& a1, int& a2, int& a3, int& a4) {
-  double r = y * 64.0;
-  double d = rint(r);
-  a1 = (int)d;
-  r = (r - d) * 128.0;
-  d = rint(r);
-  a2 = (int)d;
-  r = (r - d) * 128.0;
-  d = rint(r);
-  a3 = (int)d;
-  r = (r - d) * 128.0;
-  a4 = (int)rint(r);
+// Balanced bytes of a value scaled to |v| <= 2^31 127/128: byte p of the
+// result (from the top) is digit a_(p+1).  Adding 0x80 to the lower bytes
+// carries each byte's rounding up; the xor turns the biased bytes back into
+// two's complement.
+__device__ __forceinline__ uint32_t digits4(double v) {
+  return ((uint32_t)(int)rint(v) + 0x00808080u) ^ 0x00808080u;
+}
+
+// The digits of four consecutive tokens, one word per digit plane.
+__device__ __forceinline__ void put4(uint32_t (&w)[kDigits][4], int at, const uint32_t (&y)[4]) {
+  const uint32_t h01 = __builtin_amdgcn_perm(y[1], y[0], 0x07030602);   // tops and seconds of 0, 1
+  const uint32_t h23 = __builtin_amdgcn_perm(y[3], y[2], 0x07030602);
+  const uint32_t l01 = __builtin_amdgcn_perm(y[1], y[0], 0x05010400);   // thirds and lows
+  const uint32_t l23 = __builtin_amdgcn_perm(y[3], y[2], 0x05010400);
+  w[0][at] = __builtin_amdgcn_perm(h23, h01, 0x07060302);
+  w[1][at] = __builtin_amdgcn_perm(h23, h01, 0x05040100);
+  w[2][at] = __builtin_amdgcn_perm(l23, l01, 0x07060302);
+  w[3][at] = __builtin_amdgcn_perm(l23, l01, 0x05040100);
 }
 
 // One wave per (16-row block, 64-token step) of the sub-chunk [t0, t0 + Ts):
@@ -148,8 +162,8 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq
   const size_t at = ((size_t)s * (size_t)nrb + (size_t)b) * kBlockBytes + (size_t)lane * 16;
   uint32_t wq[kDigits][4], wd[kDigits][4];
   const bool live = row < m;
-  const double sq = live ? ldexp(1.0, -eq[row]) : 0.0;
-  const double sd = (live && Xr) ? ldexp(1.0, -ed[row]) : 0.0;
+  const double sq = live ? ldexp(1.0, 31 - eq[row]) : 0.0;
+  const double sd = (live && Xr) ? ldexp(1.0, 31 - ed[row]) : 0.0;
   const float* q = Xq + (live ? row : 0) * ldx;
   const float* x = Xr ? Xr + (live ? row : 0) * ldx : nullptr;
   // this lane's 16 tokens, 16 bytes at a time where the row allows
@@ -176,26 +190,15 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq
   }
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-#pragma unroll
-    for (int p = 0; p < kDigits; ++p) wq[p][w] = wd[p][w] = 0u;
+    uint32_t yq[4], yd[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const double a = (double)vq[4 * w + u];
-      int a1, a2, a3, a4;
-      split4(a * sq, a1, a2, a3, a4);
-      wq[0][w] |= (uint32_t)(a1 & 0xff) << (8 * u);
-      wq[1][w] |= (uint32_t)(a2 & 0xff) << (8 * u);
-      wq[2][w] |= (uint32_t)(a3 & 0xff) << (8 * u);
-      wq[3][w] |= (uint32_t)(a4 & 0xff) << (8 * u);
-      if (x) {
-        const double d = (double)vx[4 * w + u] - a;
-        split4(d * sd, a1, a2, a3, a4);
-        wd[0][w] |= (uint32_t)(a1 & 0xff) << (8 * u);
-        wd[1][w] |= (uint32_t)(a2 & 0xff) << (8 * u);
-        wd[2][w] |= (uint32_t)(a3 & 0xff) << (8 * u);
-        wd[3][w] |= (uint32_t)(a4 & 0xff) << (8 * u);
-      }
+      yq[u] = digits4(a * sq);
+      if (x) yd[u] = digits4(((double)vx[4 * w + u] - a) * sd);
     }
+    put4(wq, w, yq);
+    if (x) put4(wd, w, yd);
   }
 #pragma unroll
   for (int p = 0; p < kDigits; ++p) {
@@ -235,92 +238,139 @@ __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
 }
 
 // Steps [c0, c1) of one tile; a whole tile goes to G / E, a part to slot
-// `slot` of share r.  Two LDS stages: the loads of step c + 1 fly while step
-// c feeds the matrix cores.
+// `slot` of share r.  Two LDS stages of one step each.
+constexpr int kFirst = 5, kSecond = 3;   // loads per wave and step of the two digit groups
+template <bool kCross>
 __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_t c0, int64_t c1,
                                            int64_t r, int& slot, uint8_t* sbuf) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;   // 32x64 block of the tile
   const uint32_t te = a.tile_list[tile];
-  const bool cross = (te >> 31) != 0;
   const int64_t ti = (te >> 16) & 0x7fff, tj = te & 0xffff;
-  const uint8_t* Bsrc = cross ? a.dd : a.dq;
-  const int* eB = cross ? a.ed : a.eq;
+  const int* eB = kCross ? a.ed : a.eq;
 
-  v4i acc[5][2][4];   // [w - 2][row block][col block]
+  constexpr int kW = kCross ? 4 : 5;
+  v4i acc[kW][2][4];   // [w - 2][row block][col block]
 #pragma unroll
-  for (int c = 0; c < 5; ++c)
+  for (int c = 0; c < kW; ++c)
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
       for (int y = 0; y < 4; ++y) acc[c][x][y] = v4i{0, 0, 0, 0};
 
-  // this wave's 8 load instructions per step: blocks 8 wave .. 8 wave + 7 of
-  // the stage (0..31: A digit p = blk / 8, row block blk % 8; 32..63: B)
-  const size_t plane = (size_t)a.nsteps * (size_t)a.nrb * kBlockBytes;
-  const uint8_t* src[8];
+  // this wave's 8 load instructions per step (blocks 0..31 of the stage: A
+  // digit blk / 8, row block blk % 8; 32..63: B): five of the first group,
+  // digits 1..3 of A and 3, 4 of B, and three of the second, the others
+  // 32-bit offsets into the split buffer (at most 4 GB: gram_i8_substeps)
+  const uint32_t plane = (uint32_t)a.nsteps * (uint32_t)a.nrb * kBlockBytes;
+  const uint32_t b_at = kCross ? (uint32_t)(a.dd - a.dq) : 0u;
+  uint32_t src[8];
+  int dst[8];
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    const int blk = uwave * 8 + j;
+    const int g = uwave * kFirst + j;
+    const int blk = j < kFirst ? (g < 24 ? g : g + 24) : 24 + uwave * kSecond + (j - kFirst);
     const int half = blk >> 5, p = (blk >> 3) & 3, rb = blk & 7;
-    const uint8_t* base = half ? Bsrc : a.dq;
-    const int64_t row_block = (half ? tj : ti) * (kTile / 16) + rb;
-    src[j] = base + p * plane + (size_t)row_block * kBlockBytes;
+    const uint32_t row_block = (uint32_t)(half ? tj : ti) * (kTile / 16) + rb;
+    src[j] = (half ? b_at : 0u) + p * plane + row_block * kBlockBytes;
+    dst[j] = blk * kBlockBytes;
   }
   const size_t step_bytes = (size_t)a.nrb * kBlockBytes;
   __syncthreads();   // the previous segment's reads of both stages are done
-  auto issue = [&](int64_t c, uint8_t* dst) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      load_to_lds16(src[j] + (size_t)c * step_bytes, 16 * lane, dst + (uwave * 8 + j) * kBlockBytes);
-    }
+  // load j of step c, past the last step of that one again (so that the
+  // counted waits below hold; nothing reads it)
+  auto load = [&](int64_t c, int j) {
+    const int64_t cc = c < c1 ? c : c1 - 1;
+    load_to_lds16(a.dq + (size_t)cc * step_bytes, src[j] + 16 * lane,
+                  sbuf + ((c - c0) & 1) * kStageBytes + dst[j]);
   };
-  issue(c0, sbuf);
+  // One step is a chain of digit products (p, q), eight MFMAs each, ordered so
+  // that every fragment is read one or two products ahead of its use, and the
+  // step's stage falls into two groups of digits: the first is read by the
+  // middle of the step, the second from there to three products before the
+  // end.  At each of these two points stands a barrier, after which the
+  // group's buffer takes the same group of step c + 2, one load at a time
+  // between the products (issued together they hold up the products behind
+  // them), and the group read next has landed: its loads are a step and a
+  // half old, older than the wave's last eight.  The first fragments of the
+  // next step are read beside the last products, so no wave waits at a step's
+  // start.  4096 rows x 262144 tokens, both sums: 49 ms; 63 ms with thirteen
+  // products, every wave reading its first fragments behind one barrier per
+  // step and a step's loads issued together (with eleven products that took
+  // 57 ms, one barrier three products before the end and the loads together
+  // behind it 51 ms).  Without any loads it is 42 ms, with neither loads nor
+  // fragment reads 39 ms: the matrix cores alone, at the clock they hold.
+  v4i fa[kDigits][2], fb[2][4];
+  auto read_a = [&](const uint8_t* st, int p) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      fa[p][x] = *reinterpret_cast<const v4i*>(st + (p * 8 + wr * 2 + x) * kBlockBytes + lane * 16);
+  };
+  auto read_b = [&](const uint8_t* st, int q) {
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+      fb[q & 1][y] = *reinterpret_cast<const v4i*>(
+          st + (kPanelBlocks + q * 8 + wc * 4 + y) * kBlockBytes + lane * 16);
+  };
+  auto products = [&](int p, int q) {
+    __builtin_amdgcn_sched_barrier(0);   // the reads before go out first
+    const int w = p == 2 && q == 2 ? kW - 1 : p + q;
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) acc[w][x][y] = mfma_i8(fa[p][x], fb[q & 1][y], acc[w][x][y]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto meet = [&] {
+    __builtin_amdgcn_s_waitcnt(0x0f78);   // vmcnt(8)
+    __syncthreads();
+  };
+#pragma unroll
+  for (int j = 0; j < 8; ++j) load(c0, j);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) load(c0 + 1, j);
+  meet();
+  read_a(sbuf, 0);
+  read_b(sbuf, 3);
   for (int64_t c = c0; c < c1; ++c) {
-    uint8_t* cur = sbuf + ((c - c0) & 1) * kStageBytes;
-    wait_loads();
-    __syncthreads();   // step c is in LDS; every wave is done with step c - 1
-    if (c + 1 < c1) issue(c + 1, sbuf + ((c + 1 - c0) & 1) * kStageBytes);
-    v4i fa[kDigits][2];
-#pragma unroll
-    for (int p = 0; p < kDigits; ++p)
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-        fa[p][x] = *reinterpret_cast<const v4i*>(cur + (p * 8 + wr * 2 + x) * kBlockBytes +
-                                                 lane * 16);
-    // B fragments one digit ahead: the reads of digit q + 1 fly while the
-    // products of digit q run
-    const uint8_t* bsrc = cur + (kPanelBlocks + wc * 4) * kBlockBytes + lane * 16;
-    v4i fbn[4];
-#pragma unroll
-    for (int y = 0; y < 4; ++y) fbn[y] = *reinterpret_cast<const v4i*>(bsrc + y * kBlockBytes);
-#pragma unroll
-    for (int q = 0; q < kDigits; ++q) {
-      v4i fb[4];
-#pragma unroll
-      for (int y = 0; y < 4; ++y) fb[y] = fbn[y];
-      if (q + 1 < kDigits) {
-#pragma unroll
-        for (int y = 0; y < 4; ++y)
-          fbn[y] = *reinterpret_cast<const v4i*>(bsrc + ((q + 1) * 8 + y) * kBlockBytes);
-      }
-      __builtin_amdgcn_sched_barrier(0);   // the reads go out before the products
-#pragma unroll
-      for (int p = 0; p < kDigits; ++p) {
-        if (p + q > kDigits) continue;   // digit pairs with p + q <= 6 (1-based)
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-          for (int y = 0; y < 4; ++y)
-            acc[p + q][x][y] = mfma_i8(fa[p][x], fb[y], acc[p + q][x][y]);
-      }
-    }
+    const uint8_t* cur = sbuf + ((c - c0) & 1) * kStageBytes;
+    const uint8_t* nxt = sbuf + ((c + 1 - c0) & 1) * kStageBytes;
+    read_b(cur, 2);
+    products(0, 3);
+    read_a(cur, 1);
+    products(0, 2);
+    read_a(cur, 2);
+    products(1, 2);
+    meet();   // the first group is read, the second in LDS
+    read_b(cur, 1);
+    load(c + 2, 0);
+    if constexpr (!kCross) products(2, 2);
+    read_a(cur, 3);
+    load(c + 2, 1);
+    products(0, 1);
+    load(c + 2, 2);
+    products(1, 1);
+    read_b(cur, 0);
+    load(c + 2, 3);
+    products(2, 1);
+    load(c + 2, 4);
+    products(0, 0);
+    meet();   // the second group is read, the next step's first in LDS
+    load(c + 2, 5);
+    products(1, 0);
+    read_a(nxt, 0);    // (past the last step nothing uses them)
+    load(c + 2, 6);
+    products(2, 0);
+    read_b(nxt, 3);
+    load(c + 2, 7);
+    products(3, 0);
   }
+  wait_loads();   // none may land in the next segment's stages
 
   const bool whole = (c0 == 0 && c1 == a.nsteps);
-  double* C = cross ? a.E : a.G;
-  const double beta = cross ? a.beta_e : a.beta_g;
+  double* C = kCross ? a.E : a.G;
+  const double beta = kCross ? a.beta_e : a.beta_g;
   double* P = a.part + (r * 2 + slot) * kSlotElems;
   const int64_t I0 = ti * kTile, J0 = tj * kTile;
 #pragma unroll
@@ -333,12 +383,12 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
       for (int v = 0; v < 4; ++v) {
         const int li = wr * 32 + x * 16 + 4 * (lane >> 4) + v;
         // sum over w, smallest weight first, then the rows' power-of-two scale
-        double s = (double)acc[4][x][y][v] * 0x1p-28;
-        s += (double)acc[3][x][y][v] * 0x1p-21;
-        s += (double)acc[2][x][y][v] * 0x1p-14;
-        s += (double)acc[1][x][y][v] * 0x1p-7;
+        double s = kCross ? 0.0 : (double)acc[kW - 1][x][y][v] * 0x1p-32;
+        s += (double)acc[3][x][y][v] * 0x1p-24;
+        s += (double)acc[2][x][y][v] * 0x1p-16;
+        s += (double)acc[1][x][y][v] * 0x1p-8;
         s += (double)acc[0][x][y][v];
-        s = ldexp(s, a.eq[I0 + li] + ej - 12);
+        s = ldexp(s, a.eq[I0 + li] + ej - 14);
         if (whole) {
           const int64_t i = I0 + li, j = J0 + lj;
           if (i < a.m && j < a.m) {
@@ -361,16 +411,26 @@ __global__ __launch_bounds__(kThreads, 1) void gram_i8_kernel(I8Args a) {
   int64_t r = blockIdx.x;
   if ((a.nshare & 7) == 0) r = (r & 7) * (a.nshare >> 3) + (r >> 3);   // shares by XCD
   int slot = 0;
-  for (int64_t round = 0; round < a.n_dp; ++round)
-    i8_segment(a, round * a.nshare + r, 0, a.nsteps, r, slot, sbuf);
-  if (r >= a.nsk) return;
-  const int64_t w_end = share_begin(r + 1, a);
-  for (int64_t w = share_begin(r, a); w < w_end;) {
-    const int64_t tile = a.tile0 + w / a.nsteps;
-    const int64_t c0 = w % a.nsteps;
-    const int64_t c1 = (a.nsteps - c0) < (w_end - w) ? a.nsteps : c0 + (w_end - w);
-    i8_segment(a, tile, c0, c1, r, slot, sbuf);
-    w += c1 - c0;
+  // whole tiles round by round, then the share's run of (tile, step) pairs
+  int64_t round = 0;
+  int64_t w = r < a.nsk ? share_begin(r, a) : 0;
+  const int64_t w_end = r < a.nsk ? share_begin(r + 1, a) : 0;
+  for (;;) {
+    int64_t tile, c0 = 0, c1 = a.nsteps;
+    if (round < a.n_dp) {
+      tile = round++ * a.nshare + r;
+    } else if (w < w_end) {
+      tile = a.tile0 + w / a.nsteps;
+      c0 = w % a.nsteps;
+      if (c1 - c0 > w_end - w) c1 = c0 + (w_end - w);
+      w += c1 - c0;
+    } else {
+      break;
+    }
+    if ((a.tile_list[tile] >> 31) != 0)
+      i8_segment<true>(a, tile, c0, c1, r, slot, sbuf);
+    else
+      i8_segment<false>(a, tile, c0, c1, r, slot, sbuf);
   }
 }
 
@@ -424,7 +484,7 @@ __global__ __launch_bounds__(256) void gram_i8_fixup_kernel(I8Args a) {
 
 // 64-token steps per sub-chunk: a split buffer of about 64 m^2 bytes (the
 // size of eight fp64 m x m matrices, so it stays a fixed share of the
-// workspace), at least 1024 and at most 32768 tokens (the int32 bound above),
+// workspace), at least 1024 and at most 32704 tokens (the int32 bound above),
 // and at most 4 GB.  The sub-chunk length depends on m only, so results do not
 // depend on the workspace a caller passes.
 int64_t gram_i8_substeps(int64_t m) {
@@ -433,7 +493,7 @@ int64_t gram_i8_substeps(int64_t m) {
   int64_t budget = 64 * m * m;
   if (budget > ((int64_t)1 << 32)) budget = (int64_t)1 << 32;
   int64_t steps = budget / per_token / kStep;
-  if (steps > 32768 / kStep) steps = 32768 / kStep;
+  if (steps > 32704 / kStep) steps = 32704 / kStep;
   if (steps < 1024 / kStep) steps = 1024 / kStep;
   return steps;
 }
@@ -485,8 +545,11 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
   a.part_tile = reinterpret_cast<int*>(static_cast<char*>(scratch) +
                                        (size_t)kGramI8MaxShares * 2 * kSlotElems * sizeof(double));
   a.ntiles = tiles * (tiles + 1) / 2 + (Xr ? tiles * tiles : 0);
-  for (int64_t t0 = 0; t0 < T; t0 += max_steps * kStep) {
-    const int64_t ts = (T - t0) < max_steps * kStep ? (T - t0) : max_steps * kStep;
+  // sub-chunks of about equal length, none of a few steps only
+  const int64_t all_steps = (T + kStep - 1) / kStep, subs = (all_steps + max_steps - 1) / max_steps;
+  const int64_t sub = (all_steps + subs - 1) / subs * kStep;
+  for (int64_t t0 = 0; t0 < T; t0 += sub) {
+    const int64_t ts = (T - t0) < sub ? (T - t0) : sub;
     a.nsteps = (ts + kStep - 1) / kStep;
     const int64_t waves = a.nsteps * nrb;
     split_kernel<<<dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream>>>(
