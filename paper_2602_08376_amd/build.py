@@ -21,7 +21,7 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libojbkq.so")
 
 SOURCES = ["api.cpp", "gemm.hip", "gram.hip", "gram_i8.hip", "factor.hip", "chol_dag.hip", "quant.hip", "decode.hip",
-           "infer.hip", "permute.hip", "noalloc.hip"]
+           "infer.hip", "infer_few.hip", "permute.hip", "noalloc.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

@@ -6,27 +6,16 @@
 //
 //   pack_codes_kernel      codes [n, m] uint8 -> per-row little-endian bit
 //                          streams of `bits`-bit fields in 32-bit words
+//   dequant_weights_kernel W_hat once in fp16 (the workspace form)
 //   dequant_matmul_kernel  Y [n, T] fp32 = W_hat [n, m] X [m, T] with X in
 //                          fp16 staged in its own [k][t] layout and read
 //                          k-major by gfx950's transposing LDS read, W_hat
 //                          dequantized from the packed codes to fp16 in
 //                          LDS, products on v_mfma_f32_16x16x32_f16
-#include "device.h"
-#include "kernels.h"
+#include "infer.h"
 
 namespace ojbkq {
 namespace {
-
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-typedef float f2 __attribute__((ext_vector_type(2)));
-
-// Two float32 weights rounded to fp16 together (one packed convert, round to
-// nearest even as for a single one).
-__device__ __forceinline__ h2 to_f16x2(float lo, float hi) {
-  return __builtin_convertvector(f2{lo, hi}, h2);
-}
-typedef float f4 __attribute__((ext_vector_type(4)));
 
 // ---- packing ---------------------------------------------------------------
 
@@ -59,8 +48,6 @@ __global__ __launch_bounds__(256) void pack_codes_kernel(const uint8_t* __restri
 
 // ---- dequantize and multiply -------------------------------------------------
 
-constexpr int kTileJ = 256;    // output rows (channels) per workgroup
-constexpr int kTileT = 256;    // output columns (tokens) per workgroup
 constexpr int kStage = 64;     // k per LDS stage: two v_mfma_f32_16x16x32_f16 k-steps
 // The W_hat tile in LDS: row j of the stage's 64 features (128 bytes, no
 // padding), its eight 16-byte chunks in the order chunk c at slot c ^ (j % 8).
@@ -68,29 +55,6 @@ constexpr int kStage = 64;     // k per LDS stage: two v_mfma_f32_16x16x32_f16 k
 // 16 rows x 4 chunks then spread over all 64 banks (a padded pitch of 144 or
 // 160 bytes measured a two-way conflict on one or the other).
 __device__ __forceinline__ int aoff(int j, int c) { return j * kStage + 8 * (c ^ (j & 7)); }
-
-struct DqArgs {
-  const uint32_t* P;
-  int64_t wpr;                 // words per packed row
-  const float* S;
-  const float* Z;
-  int64_t n, m, g, G;
-  const uint16_t* X;           // fp16 bits, [m, T] with row stride ldx
-  int64_t T, ldx;
-  const int32_t* perm;         // null, or X row of packed position k = perm[k]
-  float* Y;
-  int64_t ldy;
-  int64_t tiles_n;
-  const _Float16* Wh;          // W_hat [n, mw] fp16 formed beforehand (null: dequantize in the product)
-  int64_t mw;                  // its row stride, m rounded up to a whole stage (zeros past m)
-};
-
-// Row of X that packed position k (< m) multiplies.
-__device__ __forceinline__ int64_t x_row(const DqArgs& a, int64_t k) {
-  if (!a.perm) return k;
-  const int64_t r = a.perm[k];
-  return r < 0 ? 0 : (r >= a.m ? a.m - 1 : r);
-}
 
 // 16 consecutive codes of row j starting at feature kc (a multiple of 16):
 // their bits start at kc BITS, a multiple of 16, so the first lies at bit 0
@@ -144,28 +108,28 @@ struct CodeLoader {
   }
 };
 
-constexpr int kThreads = 512;  // eight waves, each a block of the 256 x 256 output tile
-
+// Output tiles of kTile channels x kTile tokens, 256 with eight waves or 128
+// with four (launch_dq says when).
 // The activation tile in LDS keeps X's own layout, row k (a feature) with
-// the tile's 256 tokens contiguous (512 bytes, no padding, so that two rows
-// fill the 1 KB that one direct-to-LDS load of a wave writes).  Its 16-token
+// the tile's tokens contiguous (512 or 256 bytes, no padding, so that two or
+// four rows fill the 1 KB that one direct-to-LDS load of a wave writes).  Its 16-token
 // blocks are XOR-swizzled by f(k) = (k % 4) + 4 (bit 3 of k), so the 8 rows
 // that half a wave reads in one transposing read (rows 8g .. 8g + 3 for lane
 // groups g = 0, 1, or 2, 3) fall in 64 distinct banks.  Offset (halves) of
 // token t of row k:
 __device__ __forceinline__ int xswz(int k) { return (k & 3) | (((k >> 3) & 1) << 2); }
+template <int kTile>
 __device__ __forceinline__ int xoff(int k, int t) {
-  return k * kTileT + 16 * ((t >> 4) ^ xswz(k)) + (t & 15);
+  return k * kTile + 16 * ((t >> 4) ^ xswz(k)) + (t & 15);
 }
-
-typedef short s4 __attribute__((ext_vector_type(4)));
 
 // Four features of one token for an MFMA B operand, straight from the
 // activation tile with gfx950's transposing LDS read: lane i of each group of
 // 16 points at row k0 + i / 4, tokens t0 + 4 (i % 4) .. + 3 (t0 a multiple of
 // 16), and receives rows k0 .. k0 + 3 of token t0 + i.
+template <int kTile>
 __device__ __forceinline__ s4 read_tr(const _Float16* B, int k0, int t0, int i) {
-  const _Float16* p = B + xoff(k0 + (i >> 2), t0 + 4 * (i & 3));
+  const _Float16* p = B + xoff<kTile>(k0 + (i >> 2), t0 + 4 * (i & 3));
   return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
       (s4 __attribute__((address_space(3)))*)(const_cast<_Float16*>(p)));
 }
@@ -173,9 +137,9 @@ __device__ __forceinline__ s4 read_tr(const _Float16* B, int k0, int t0, int i) 
 // Output tile of this workgroup.  Workgroups are dealt to the eight XCDs
 // round-robin by blockIdx, so the tiles are renumbered to give each XCD a
 // contiguous run, walked in groups of kGroupJ channel tiles with the token
-// tiles outer: the 32 workgroups an XCD runs at once then cover 8 channel
-// tiles x 4 token tiles and share those W_hat and activation panels in its
-// L2.
+// tiles outer: the 32 (64 of the small ones) workgroups an XCD runs at once
+// then cover 8 x 4 (8 x 8) tiles and share those W_hat and activation panels
+// in its L2.
 constexpr int64_t kGroupJ = 8;
 __device__ __forceinline__ void dq_tile(int64_t tiles_n, int64_t& tj, int64_t& tt) {
   const int64_t nb = gridDim.x, tiles_t = nb / tiles_n;
@@ -188,33 +152,38 @@ __device__ __forceinline__ void dq_tile(int64_t tiles_n, int64_t& tj, int64_t& t
   tt = r / rows;
 }
 
-// With kPre, W_hat comes ready-made from a.Wh (loaded straight into LDS like
-// the activations) and BITS is unused; every output element then takes the same
-// products in the same order as with the codes, so the two agree bit for bit.
-template <int BITS, bool VEC, bool kPre>
-__global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
+// With kPre, W_hat comes ready-made from a.Wh (loaded straight into LDS) and
+// BITS is unused; every output element takes the same products in the same
+// order with or without it and with either tile, so all agree bit for bit.
+// kDirect (with kPre, rows of X 16-byte aligned and T a multiple of 8): the
+// activations too are loaded straight into LDS.  Otherwise they go through
+// registers, eight tokens per load at any alignment.
+template <int BITS, int kTile, bool kPre, bool kDirect>
+__global__ __launch_bounds__(2 * kTile, kTile == 256 ? 1 : 2) void dequant_matmul_kernel(
+    DqArgs a) {
   // two buffers: the waves dequantize and stage step s + 1 into one while
   // their MFMAs read step s from the other, with one barrier per step
-  __shared__ __align__(16) _Float16 sA[2][kTileJ * kStage];   // W_hat tile: row j, k contiguous
-  __shared__ __align__(16) _Float16 sB[2][kStage * kTileT];   // X tile: row k, tokens contiguous
+  __shared__ __align__(16) _Float16 sA[2][kTile * kStage];   // W_hat tile: row j, k contiguous
+  __shared__ __align__(16) _Float16 sB[2][kStage * kTile];   // X tile: row k, tokens contiguous
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // each wave's block: NX x NY products of 16 x 16, 2 x 4 blocks of 128
   // channels x 64 tokens with W_hat ready-made (fewer transposing reads per
-  // product), 4 x 2 blocks of 64 x 128 when dequantizing (fewer registers)
-  constexpr int NX = kPre ? 8 : 4, NY = 32 / NX, kWc = 16 / NY;
+  // product), 4 x 2 blocks of 64 x 128 when dequantizing (fewer registers);
+  // in the small tile 2 x 2 blocks of 64 x 64
+  constexpr int NX = kPre && kTile == 256 ? 8 : 4, NY = kTile == 256 ? 32 / NX : 4;
+  constexpr int kWc = kTile / 16 / NY;
   const int wr = wave / kWc, wc = wave % kWc;
   int64_t tj, tt;
   dq_tile(a.tiles_n, tj, tt);
-  const int64_t J0 = tj * kTileJ, T0 = tt * kTileT;
+  const int64_t J0 = tj * kTile, T0 = tt * kTile;
 
   // A loader: thread -> row tid / 2, two runs of 16 codes of the stage,
   // 32 (tid % 2) + 16 h .. + 15, h = 0, 1 (each inside one group: g % 16 == 0).
   const int ar = tid >> 1, ac = tid & 1;
   const int64_t aj = J0 + ar;
-  // The stage is interior when its 64 features and the tile's rows and
-  // tokens all exist (the same for every lane): no clamping or masking then.
-  const bool tile_in = J0 + kTileJ <= a.n && T0 + kTileT <= a.T;
-  auto interior = [&](int64_t k0) { return VEC && tile_in && k0 + kStage <= a.m; };
+  // whether all 64 features of a stage exist (the same for every lane); all
+  // do but in a last ragged stage
+  auto interior = [&](int64_t k0) { return k0 + kStage <= a.m; };
 
   // this thread's channel row of the scales and zero points
   const float* const s_row = a.S + (aj < a.n ? aj : a.n - 1) * a.G;
@@ -239,69 +208,83 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
     sb = s_row[gb];
     zb = z_row[gb];
   };
-  // kPre: the X row of each of this thread's four loads of a stage (tile
-  // rows 2 (4 w + q) + l / 32: see fetch_x), read right after the loads of
-  // the stage before it are issued, so that with a permutation its entries
-  // arrive a whole step before the rows they address and no activation load
-  // waits on them.  (Without kPre the registers are needed for
-  // dequantizing: fetch_xv reads a stage's four entries together, then the rows.)
+  // kDirect: the X row of each of this thread's four loads of a stage (see
+  // fetch_x), read right after the loads of the stage before it are issued,
+  // so that with a permutation its entries arrive a whole step before the
+  // rows they address and no activation load waits on them.  (Otherwise
+  // fetch_xv reads a stage's four entries together, then the rows.)
   // The entries are kept as read and clamped where used (any arithmetic on
   // them here, or a second definition of the registers on the path without
   // a permutation, would make the compiler wait for the loads at once).
+  constexpr int kSlots = kTile / 8, kRowsPer = 64 / kSlots;   // 16-byte slots of a tile row, rows per load
   int32_t prow[4] = {0, 0, 0, 0};
   auto rows_for = [&](int64_t k0) {
     if (a.perm) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int64_t k = k0 + 2 * (4 * wave + q) + (lane >> 5);
+        const int64_t k = k0 + kRowsPer * (4 * wave + q) + lane / kSlots;
         prow[q] = a.perm[k < a.m ? k : a.m - 1];
       }
     }
   };
-  // kPre: an interior stage of X straight into LDS: wave w's load q covers tile
-  // rows 2 (4 w + q) and + 1 (1 KB); lane l fills 16-byte slot l % 32 of row
-  // l / 32 of it, i.e. the 8 tokens of half (l % 2) of the swizzled block
-  // (l % 32) / 2.
+  // kDirect: an interior stage of X straight into LDS: wave w's load q covers
+  // tile rows kRowsPer (4 w + q) .. (1 KB); lane l fills 16-byte slot
+  // l % kSlots of row l / kSlots of it, i.e. the 8 tokens of half (l % 2) of
+  // the swizzled block (l % kSlots) / 2.  Tokens past the last one (whole
+  // slots: T % 8 == 0) repeat the row's first ones; nothing of theirs is stored.
   auto fetch_x = [&](int64_t k0, int buf) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int r0 = 2 * (4 * wave + q), r = r0 + (lane >> 5);
-      const int u = ((lane & 31) >> 1) ^ xswz(r);
+      const int r0 = kRowsPer * (4 * wave + q), r = r0 + lane / kSlots;
+      const int u = ((lane % kSlots) >> 1) ^ xswz(r);
+      const int64_t t = T0 + 16 * u + 8 * (lane & 1);
       const int64_t row =
           !a.perm ? k0 + r : (prow[q] < 0 ? 0 : (prow[q] >= a.m ? a.m - 1 : prow[q]));
-      load_to_lds16_at(a.X + row * a.ldx + T0 + 16 * u + 8 * (lane & 1),
-                       sB[buf] + r0 * kTileT);
+      load_to_lds16_at(a.X + row * a.ldx + (t < a.T ? t : 0), sB[buf] + r0 * kTile);
     }
   };
-  // Without kPre (the registers are needed for dequantizing): the same
-  // stage through registers, thread -> tokens 8 (tid % 32) .. + 7 of rows
-  // tid / 32 + 16 q, one 16-byte load each, held (a vector, not an array:
-  // an array captured by these lambdas is moved to LDS) while the products
-  // run, then stored.
-  const int bc = tid & 31, br = tid >> 5;
+  // Otherwise (and for a ragged last stage) through registers: thread ->
+  // tokens 8 (tid % kSlots) .. + 7 of rows tid / kSlots + 16 q, one 16-byte
+  // load each at whatever alignment the row has, held (a vector, not an
+  // array: an array captured by these lambdas is moved to LDS) while the
+  // products run, then stored.  Features past the last one are zero.  Eight
+  // tokens that reach past the last one are read on into the next row (they
+  // feed only outputs never stored), in X's last row one by one.
+  const int bc = tid % kSlots, br = tid / kSlots;
   typedef uint32_t Runs __attribute__((ext_vector_type(16)));
+  typedef uint32_t Any4 __attribute__((ext_vector_type(4), aligned(2)));
   Runs xv;
-  const uint16_t* const xv0 = a.X + (int64_t)br * a.ldx + T0 + 8 * bc;
+  const int64_t xt = T0 + 8 * bc;
   auto fetch_xv = [&](int64_t k0) {
-    const uint16_t* src[4];
+    int64_t xr[4];
     if (a.perm) {
       // the four entries first, so that their loads overlap (an entry read
       // where its row is loaded makes each row wait for its own entry)
       int32_t pr[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) pr[q] = a.perm[k0 + br + 16 * q];
-#pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int64_t r = pr[q] < 0 ? 0 : (pr[q] >= a.m ? a.m - 1 : pr[q]);
-        src[q] = a.X + r * a.ldx + T0 + 8 * bc;
+        const int64_t k = k0 + br + 16 * q;
+        pr[q] = a.perm[k < a.m ? k : a.m - 1];
       }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xr[q] = pr[q] < 0 ? 0 : (pr[q] >= a.m ? a.m - 1 : pr[q]);
     } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) src[q] = xv0 + (k0 + 16 * q) * a.ldx;
+      for (int q = 0; q < 4; ++q) xr[q] = k0 + br + 16 * q;
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const uint4 v = *reinterpret_cast<const uint4*>(src[q]);
+      Any4 v = Any4{0u, 0u, 0u, 0u};
+      if (k0 + br + 16 * q < a.m && xt < a.T) {
+        const uint16_t* src = a.X + xr[q] * a.ldx + xt;
+        if (xt + 8 <= a.T || xr[q] + 1 < a.m) {
+          v = *reinterpret_cast<const Any4*>(src);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (xt + e < a.T) v[e / 2] |= (uint32_t)src[e] << (16 * (e & 1));
+        }
+      }
       xv[4 * q] = v.x;
       xv[4 * q + 1] = v.y;
       xv[4 * q + 2] = v.z;
@@ -311,7 +294,7 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
   auto store_xv = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<uint4*>(sB[buf] + xoff(br + 16 * q, 8 * bc)) =
+      *reinterpret_cast<uint4*>(sB[buf] + xoff<kTile>(br + 16 * q, 8 * bc)) =
           make_uint4(xv[4 * q], xv[4 * q + 1], xv[4 * q + 2], xv[4 * q + 3]);
   };
   // kPre: the stage of W_hat straight into LDS: wave w's load q covers tile
@@ -324,24 +307,6 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
       const int r0 = 8 * (4 * wave + q), r = r0 + (lane >> 3);
       const int64_t j = J0 + r < a.n ? J0 + r : a.n - 1;
       load_to_lds16_at(a.Wh + j * a.mw + k0 + 8 * ((lane & 7) ^ (r & 7)), sA[buf] + r0 * kStage);
-    }
-  };
-  // an edge stage of X, element by element, zero past the last feature or
-  // token, with the thread mapping of fetch_xv
-  auto stage_x_edge = [&](int64_t k0, _Float16* B) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = br + 16 * q;
-      const int64_t k = k0 + r;
-      h8 u;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int64_t t = T0 + 8 * bc + e;
-        uint16_t b = 0;
-        if (t < a.T && k < a.m) b = a.X[x_row(a, k) * a.ldx + t];
-        u[e] = __builtin_bit_cast(_Float16, b);
-      }
-      *reinterpret_cast<h8*>(B + xoff(r, 8 * bc)) = u;
     }
   };
   // W_hat = fp16(fp32(s (q - z))): the float32 weight of code c of a run,
@@ -418,7 +383,7 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
   // The products of the stage in buffer `cur` (two k-steps of 32, each NX x NY
   // tiles of v_mfma_f32_16x16x32_f16).  With `dq`, run ks of the next stage
   // (at kn, into buffer `nxt`) is dequantized beside k-step ks: one weight
-  // after each product, its 16-byte LDS stores as they fill, the order kept
+  // after every or every other product, its 16-byte LDS stores as they fill, the order kept
   // by scheduling barriers so that the vector ALU and the matrix cores work
   // side by side.  No masks: past the last feature mask_tail zeroes the
   // weights afterwards, and rows past the last channel feed only output rows
@@ -435,7 +400,7 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
     // B fragment: features 32 ks + 8 g16 .. + 7 of token 16 (NY wc + y) + i16
     auto load_b = [&](int ks, int y) {
       const int k0 = 32 * ks + 8 * g16, t0 = 16 * (NY * wc + y);
-      const s4 lo = read_tr(B, k0, t0, i16), hi = read_tr(B, k0 + 4, t0, i16);
+      const s4 lo = read_tr<kTile>(B, k0, t0, i16), hi = read_tr<kTile>(B, k0 + 4, t0, i16);
       return __builtin_bit_cast(h8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
     // B one token block ahead of its products; in the last token block of
@@ -461,10 +426,11 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
           acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[x], fbc, acc[x][y], 0, 0, 0);
           if (ks == 0 && y + 1 == NY) fa[x] = load_a(1, x);
           const int i = NX * y + x;
-          if (!kPre && (i & 1) == 0) {
+          constexpr int kPer = NX * NY / 16;   // products per weight
+          if (!kPre && i % kPer == 0) {
             // (computed on the last stage too, where nothing is stored: no
             // branch around each weight)
-            const int c = i >> 1;   // code c of run ks
+            const int c = i / kPer;   // code c of run ks
             const float p = ks ? weight(c1, s1, z1, c, 16, false) : weight(c0, s0, z0, c, 16, false);
             if ((c & 1) == 0) {
               pe = p;
@@ -496,16 +462,14 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
   } else {
     fetch_codes(0, c0, c1, s0, z0, s1, z1);
   }
-  if constexpr (kPre) rows_for(0);
-  if (!interior(0)) {
-    stage_x_edge(0, sB[0]);
-  } else if constexpr (kPre) {
+  if (kDirect && interior(0)) {
+    rows_for(0);
     fetch_x(0, 0);
   } else {
     fetch_xv(0);
     store_xv(0);
   }
-  if constexpr (kPre) rows_for(kStage);
+  if constexpr (kDirect) rows_for(kStage);
   if constexpr (!kPre) {
     dequant_all(0, 0);
     if (nst > 1) fetch_codes(kStage, n0, n1, ns0, nz0, ns1, nz1);
@@ -529,25 +493,27 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
       z1 = nz1;
       if (st + 2 < nst) fetch_codes(kn + kStage, n0, n1, ns0, nz0, ns1, nz1);
     }
-    const bool in_n = more && interior(kn);
+    const bool in_n = interior(kn);
     // buffer nxt was last read in step st - 1, before the barrier that ended it
-    if (in_n) {
-      if constexpr (kPre)
-        fetch_x(kn, nxt);
-      else
+    if (more) {
+      if constexpr (kDirect) {
+        if (in_n) fetch_x(kn, nxt);
+      } else {
         fetch_xv(kn);
+      }
     }
-    if constexpr (kPre) {
+    if constexpr (kDirect) {
       if (st + 2 < nst) rows_for(kn + kStage);
     }
     compute(cur, nxt, kn, more);
     if (more) {
-      if (!in_n) {
-        stage_x_edge(kn, sB[nxt]);
-        if constexpr (!kPre) mask_tail(kn, nxt);
-      }
-      else if constexpr (!kPre)
+      if constexpr (!kDirect) {
         store_xv(nxt);
+        if (!kPre && !in_n) mask_tail(kn, nxt);
+      } else if (!in_n) {
+        fetch_xv(kn);
+        store_xv(nxt);
+      }
     }
     // (also keeps the compiler from waiting for this step's code loads at
     // the top of the next step: it cannot pair their conditions)
@@ -570,21 +536,34 @@ __global__ __launch_bounds__(kThreads, 1) void dequant_matmul_kernel(DqArgs a) {
 
 // ---- the product with W_hat formed beforehand ----------------------------------
 
-template <int BITS>
-hipError_t launch_dq(const DqArgs& a, int64_t tiles, hipStream_t s) {
-  // 16-byte activation loads: rows 16-byte aligned (X 16-byte aligned, ldx % 8 == 0)
-  const bool vec = reinterpret_cast<uintptr_t>(a.X) % 16 == 0 && a.ldx % 8 == 0;
+template <int BITS, int kTile>
+hipError_t launch_dq_tile(DqArgs a, hipStream_t s) {
+  a.tiles_n = (a.n + kTile - 1) / kTile;
+  const int64_t tiles = a.tiles_n * ((a.T + kTile - 1) / kTile);
+  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)tiles), block(2 * kTile);
   if (a.Wh) {
-    if (vec)
-      dequant_matmul_kernel<1, true, true><<<dim3((unsigned)tiles), dim3(kThreads), 0, s>>>(a);
+    const bool direct =
+        reinterpret_cast<uintptr_t>(a.X) % 16 == 0 && a.ldx % 8 == 0 && a.T % 8 == 0;
+    if (direct)
+      dequant_matmul_kernel<1, kTile, true, true><<<grid, block, 0, s>>>(a);
     else
-      dequant_matmul_kernel<1, false, true><<<dim3((unsigned)tiles), dim3(kThreads), 0, s>>>(a);
-  } else if (vec) {
-    dequant_matmul_kernel<BITS, true, false><<<dim3((unsigned)tiles), dim3(kThreads), 0, s>>>(a);
+      dequant_matmul_kernel<1, kTile, true, false><<<grid, block, 0, s>>>(a);
   } else {
-    dequant_matmul_kernel<BITS, false, false><<<dim3((unsigned)tiles), dim3(kThreads), 0, s>>>(a);
+    dequant_matmul_kernel<BITS, kTile, false, false><<<grid, block, 0, s>>>(a);
   }
   return hipGetLastError();
+}
+
+// A round of 256-wide tiles (one per CU) against rounds of 128-wide ones (two
+// per CU, a round of them 0.65 of the time): n = m = 4096, us for 256 / 128:
+// T = 1000: 118 / 77, 2048: 122 / 94, 4096: 140 / 167, 32768: 1067 / 1372.
+template <int BITS>
+hipError_t launch_dq(const DqArgs& a, hipStream_t s) {
+  const int64_t big = (a.n + 255) / 256 * ((a.T + 255) / 256);
+  const int64_t small = (a.n + 127) / 128 * ((a.T + 127) / 128);
+  return 100 * ((big + 255) / 256) <= 65 * ((small + 511) / 512) ? launch_dq_tile<BITS, 256>(a, s)
+                                                                 : launch_dq_tile<BITS, 128>(a, s);
 }
 
 // W_hat [n, mw] fp16 = fp16(fp32(s (q - z))) of the packed codes, zeros for
@@ -666,11 +645,15 @@ hipError_t launch_dequant_matmul(const uint32_t* P, const float* S, const float*
   a.perm = perm;
   a.Y = Y;
   a.ldy = ldy;
-  a.tiles_n = (n + kTileJ - 1) / kTileJ;
+  a.tiles_n = 0;
   a.mw = (m + kStage - 1) / kStage * kStage;
   a.Wh = nullptr;
-  const int64_t tiles = a.tiles_n * ((T + kTileT - 1) / kTileT);
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  // few tokens or a narrow layer: up to two workgroups of 64 channels x 64
+  // tokens per CU.  One pass over the codes, the workspace not needed.  (us at
+  // m = 4096, 4 bits, against the 128-wide tiles below with W_hat once: n =
+  // 4096, T = 512: 69 / 75, T = 1000: 137 / 77; n = 14336, T = 128: 69 / 84,
+  // T = 256: 133 / 87.)
+  if ((n + 63) / 64 * ((T + 63) / 64) <= 512) return launch_dequant_few(a, bits, stream);
   if (workspace) {
     // W_hat once, then the product reads it instead of dequantizing every tile
     _Float16* W = static_cast<_Float16*>(workspace);
@@ -688,17 +671,17 @@ hipError_t launch_dequant_matmul(const uint32_t* P, const float* S, const float*
     }
     if (e != hipSuccess) return e;
     a.Wh = W;
-    return launch_dq<1>(a, tiles, stream);
+    return launch_dq<1>(a, stream);
   }
   switch (bits) {
-    case 1: return launch_dq<1>(a, tiles, stream);
-    case 2: return launch_dq<2>(a, tiles, stream);
-    case 3: return launch_dq<3>(a, tiles, stream);
-    case 4: return launch_dq<4>(a, tiles, stream);
-    case 5: return launch_dq<5>(a, tiles, stream);
-    case 6: return launch_dq<6>(a, tiles, stream);
-    case 7: return launch_dq<7>(a, tiles, stream);
-    case 8: return launch_dq<8>(a, tiles, stream);
+    case 1: return launch_dq<1>(a, stream);
+    case 2: return launch_dq<2>(a, stream);
+    case 3: return launch_dq<3>(a, stream);
+    case 4: return launch_dq<4>(a, stream);
+    case 5: return launch_dq<5>(a, stream);
+    case 6: return launch_dq<6>(a, stream);
+    case 7: return launch_dq<7>(a, stream);
+    case 8: return launch_dq<8>(a, stream);
     default: return hipErrorInvalidValue;
   }
 }
