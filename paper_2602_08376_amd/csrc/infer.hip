@@ -19,12 +19,128 @@ namespace {
 
 // ---- packing ---------------------------------------------------------------
 
-// One thread per output word: word w of row j holds bits [32 w, 32 w + 32)
-// of the row's stream, code i at bits [i bits, (i + 1) bits).
+// One thread per 32 codes of a row, which fill `BITS` whole words: word w of
+// row j holds bits [32 w, 32 w + 32) of the row's stream, code i at bits
+// [i BITS, (i + 1) BITS).  Bound by memory; the codes come as two 16-byte
+// loads at whatever alignment the row has, or with a permutation byte by byte
+// from the rows' copy in LDS (pack_perm_kernel).
+template <int BITS>
+__device__ __forceinline__ void pack32(const uint32_t (&c)[8], uint32_t (&w)[BITS]) {
+#pragma unroll
+  for (int q = 0; q < BITS; ++q) w[q] = 0u;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    const uint32_t q = (c[i / 4] >> (8 * (i % 4))) & ((1u << BITS) - 1u);
+    const int b = i * BITS;
+    w[b / 32] |= q << (b % 32);
+    if (b % 32 + BITS > 32) w[b / 32 + 1 < BITS ? b / 32 + 1 : 0] |= q >> (32 - b % 32);
+  }
+}
+
+template <int BITS>
+__device__ __forceinline__ void store_words(uint32_t* P, int64_t at, int64_t wpr,
+                                            const uint32_t (&w)[BITS]) {
+  if (at + BITS <= wpr) {
+    typedef uint32_t Any __attribute__((ext_vector_type(BITS), aligned(4)));
+    Any v;
+#pragma unroll
+    for (int q = 0; q < BITS; ++q) v[q] = w[q];
+    *reinterpret_cast<Any*>(P + at) = v;
+  } else {
+#pragma unroll
+    for (int q = 0; q < BITS; ++q)
+      if (at + q < wpr) P[at + q] = w[q];
+  }
+}
+
+template <int BITS>
 __global__ __launch_bounds__(256) void pack_codes_kernel(const uint8_t* __restrict__ codes,
-                                                         int64_t n, int64_t m, int bits,
-                                                         const int32_t* __restrict__ perm,
-                                                         int64_t wpr, uint32_t* __restrict__ P) {
+                                                         int64_t n, int64_t m, int64_t wpr,
+                                                         uint32_t* __restrict__ P) {
+  const int64_t units = (m + 31) / 32, total = n * units;
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total;
+       e += (int64_t)gridDim.x * 256) {
+    const int64_t j = e / units, u = e % units;
+    const uint8_t* src = codes + j * m + 32 * u;
+    uint32_t c[8], w[BITS];
+    if (32 * u + 32 <= m) {
+      typedef uint32_t Any4 __attribute__((ext_vector_type(4), aligned(1)));
+      const Any4 lo = *reinterpret_cast<const Any4*>(src);
+      const Any4 hi = *reinterpret_cast<const Any4*>(src + 16);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        c[q] = lo[q];
+        c[4 + q] = hi[q];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) c[q] = 0u;
+#pragma unroll
+      for (int i = 0; i < 32; ++i)
+        if (32 * u + i < m) c[i / 4] |= (uint32_t)src[i] << (8 * (i % 4));
+    }
+    pack32<BITS>(c, w);
+    store_words<BITS>(P + j * wpr, u * BITS, wpr, w);
+  }
+}
+
+// `rows` rows of m codes per workgroup, copied to (dynamic) LDS.  A thread
+// reads the permutation of its 32 positions once and packs them for every
+// row (with up to 8 positions' worth of threads to a row, every other row and
+// so on).
+constexpr int kPackLds = 65536;
+template <int BITS>
+__global__ __launch_bounds__(256) void pack_perm_kernel(const uint8_t* __restrict__ codes,
+                                                        int64_t n, int m,
+                                                        const int32_t* __restrict__ perm,
+                                                        int rows, int64_t wpr,
+                                                        uint32_t* __restrict__ P) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  const int64_t j0 = (int64_t)blockIdx.x * rows;
+  const int here = (int)(n - j0 < rows ? n - j0 : rows);
+  const int bytes = here * m;
+  const uint8_t* src = codes + j0 * m;
+  typedef uint32_t Any4 __attribute__((ext_vector_type(4), aligned(1)));
+  for (int b = 16 * (int)threadIdx.x; b < bytes; b += 16 * 256) {
+    if (b + 16 <= bytes) {
+      const Any4 v = *reinterpret_cast<const Any4*>(src + b);
+      *reinterpret_cast<uint4*>(lds + b) = make_uint4(v.x, v.y, v.z, v.w);
+    } else {
+      for (int i = b; i < bytes; ++i) lds[i] = src[i];
+    }
+  }
+  __syncthreads();
+  const int units = (m + 31) / 32;
+  const int split = units < 256 ? 256 / units : 1;   // threads that share a unit's rows
+  for (int e = threadIdx.x; e < units * split; e += 256) {
+    const int u = e % units;
+    int at[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+      const int p = perm[32 * u + i < m ? 32 * u + i : m - 1];
+      at[i] = p < 0 ? 0 : (p >= m ? m - 1 : p);
+    }
+    for (int r = e / units; r < here; r += split) {
+      uint32_t c[8], w[BITS];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) c[q] = 0u;
+#pragma unroll
+      for (int i = 0; i < 32; ++i) {
+        const uint32_t v = lds[r * m + at[i]];
+        c[i / 4] |= (32 * u + i < m ? v : 0u) << (8 * (i % 4));
+      }
+      pack32<BITS>(c, w);
+      store_words<BITS>(P + (j0 + r) * wpr, u * BITS, wpr, w);
+    }
+  }
+}
+
+// The same for longer rows, one thread per output word, codes read in place.
+__global__ __launch_bounds__(256) void pack_perm_long_kernel(const uint8_t* __restrict__ codes,
+                                                             int64_t n, int64_t m, int bits,
+                                                             const int32_t* __restrict__ perm,
+                                                             int64_t wpr,
+                                                             uint32_t* __restrict__ P) {
   const int64_t total = n * wpr;
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * 256) {
@@ -33,17 +149,38 @@ __global__ __launch_bounds__(256) void pack_codes_kernel(const uint8_t* __restri
     int64_t i = b0 / bits;                           // first code touching it
     uint32_t v = 0;
     for (; i < m && i * bits < b0 + 32; ++i) {
-      int64_t src = i;
-      if (perm) {
-        src = perm[i];
-        src = src < 0 ? 0 : (src >= m ? m - 1 : src);
-      }
+      int64_t src = perm[i];
+      src = src < 0 ? 0 : (src >= m ? m - 1 : src);
       const uint64_t q = codes[j * m + src] & ((1u << bits) - 1u);
       const int64_t sh = i * bits - b0;              // may be negative for the first code
       v |= (uint32_t)(sh >= 0 ? (q << sh) : (q >> -sh));
     }
     P[e] = v;
   }
+}
+
+template <int BITS>
+hipError_t launch_pack(const uint8_t* codes, int64_t n, int64_t m, const int32_t* perm,
+                       uint32_t* P, hipStream_t stream) {
+  const int64_t wpr = packed_words(m, BITS);
+  if (!perm) {
+    const int64_t blocks = (n * ((m + 31) / 32) + 255) / 256;
+    pack_codes_kernel<BITS><<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0,
+                              stream>>>(codes, n, m, wpr, P);
+  } else if (m <= kPackLds) {
+    // about eight rows (enough that the permutation is read from L1), fewer
+    // where that would leave CUs without a workgroup or not fit
+    int64_t rows = kPackLds / m < 8 ? kPackLds / m : 8;
+    while (rows > 1 && (n + rows - 1) / rows < 1024) rows /= 2;
+    const int64_t blocks = (n + rows - 1) / rows;
+    pack_perm_kernel<BITS><<<dim3((unsigned)blocks), dim3(256), (size_t)(rows * m), stream>>>(
+        codes, n, (int)m, perm, (int)rows, wpr, P);
+  } else {
+    const int64_t blocks = (n * wpr + 255) / 256;
+    pack_perm_long_kernel<<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0,
+                            stream>>>(codes, n, m, BITS, perm, wpr, P);
+  }
+  return hipGetLastError();
 }
 
 // ---- dequantize and multiply -------------------------------------------------
@@ -612,12 +749,18 @@ int64_t packed_words(int64_t m, int bits) { return (m * bits + 31) / 32; }
 
 hipError_t launch_pack_codes(const uint8_t* codes, int64_t n, int64_t m, int bits,
                              const int32_t* perm, uint32_t* P, hipStream_t stream) {
-  const int64_t total = n * packed_words(m, bits);
-  if (total <= 0) return hipSuccess;
-  const int64_t blocks = (total + 255) / 256;
-  pack_codes_kernel<<<dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0, stream>>>(
-      codes, n, m, bits, perm, packed_words(m, bits), P);
-  return hipGetLastError();
+  if (n <= 0 || m <= 0) return hipSuccess;
+  switch (bits) {
+    case 1: return launch_pack<1>(codes, n, m, perm, P, stream);
+    case 2: return launch_pack<2>(codes, n, m, perm, P, stream);
+    case 3: return launch_pack<3>(codes, n, m, perm, P, stream);
+    case 4: return launch_pack<4>(codes, n, m, perm, P, stream);
+    case 5: return launch_pack<5>(codes, n, m, perm, P, stream);
+    case 6: return launch_pack<6>(codes, n, m, perm, P, stream);
+    case 7: return launch_pack<7>(codes, n, m, perm, P, stream);
+    case 8: return launch_pack<8>(codes, n, m, perm, P, stream);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 size_t dequant_matmul_workspace_bytes(int64_t n, int64_t m) {
