@@ -346,7 +346,7 @@ __global__ __launch_bounds__(2 * kTile, kTile == 256 ? 1 : 2) void dequant_matmu
     zb = z_row[gb];
   };
   // kDirect: the X row of each of this thread's four loads of a stage (see
-  // fetch_x), read right after the loads of the stage before it are issued,
+  // load_x), read right after the loads of the stage before it are issued,
   // so that with a permutation its entries arrive a whole step before the
   // rows they address and no activation load waits on them.  (Otherwise
   // fetch_xv reads a stage's four entries together, then the rows.)
@@ -362,22 +362,6 @@ __global__ __launch_bounds__(2 * kTile, kTile == 256 ? 1 : 2) void dequant_matmu
         const int64_t k = k0 + kRowsPer * (4 * wave + q) + lane / kSlots;
         prow[q] = a.perm[k < a.m ? k : a.m - 1];
       }
-    }
-  };
-  // kDirect: an interior stage of X straight into LDS: wave w's load q covers
-  // tile rows kRowsPer (4 w + q) .. (1 KB); lane l fills 16-byte slot
-  // l % kSlots of row l / kSlots of it, i.e. the 8 tokens of half (l % 2) of
-  // the swizzled block (l % kSlots) / 2.  Tokens past the last one (whole
-  // slots: T % 8 == 0) repeat the row's first ones; nothing of theirs is stored.
-  auto fetch_x = [&](int64_t k0, int buf) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r0 = kRowsPer * (4 * wave + q), r = r0 + lane / kSlots;
-      const int u = ((lane % kSlots) >> 1) ^ xswz(r);
-      const int64_t t = T0 + 16 * u + 8 * (lane & 1);
-      const int64_t row =
-          !a.perm ? k0 + r : (prow[q] < 0 ? 0 : (prow[q] >= a.m ? a.m - 1 : prow[q]));
-      load_to_lds16_at(a.X + row * a.ldx + (t < a.T ? t : 0), sB[buf] + r0 * kTile);
     }
   };
   // Otherwise (and for a ragged last stage) through registers: thread ->
@@ -589,73 +573,168 @@ __global__ __launch_bounds__(2 * kTile, kTile == 256 ? 1 : 2) void dequant_matmu
     }
   };
 
-  // Stage st computes from buffer st % 2 while the activations (and W_hat)
-  // of stage st + 1 load straight into the other buffer, or its codes are
-  // dequantized into it beside the products.  vmcnt(0) before each barrier:
-  // the direct loads have landed in LDS.
   const int64_t nst = (a.m + kStage - 1) / kStage;
-  if constexpr (kPre) {
-    fetch_w(0, 0);
-  } else {
-    fetch_codes(0, c0, c1, s0, z0, s1, z1);
-  }
-  if (kDirect && interior(0)) {
-    rows_for(0);
-    fetch_x(0, 0);
-  } else {
-    fetch_xv(0);
-    store_xv(0);
-  }
-  if constexpr (kDirect) rows_for(kStage);
-  if constexpr (!kPre) {
-    dequant_all(0, 0);
-    if (nst > 1) fetch_codes(kStage, n0, n1, ns0, nz0, ns1, nz1);
-  }
-  __builtin_amdgcn_s_waitcnt(0x0f70);
-  __syncthreads();
-  for (int64_t st = 0; st < nst; ++st) {
-    const int cur = (int)(st & 1), nxt = cur ^ 1;
-    const int64_t kn = (st + 1) * kStage;
-    const bool more = st + 1 < nst;
-    if constexpr (kPre) {
-      if (more) fetch_w(kn, nxt);
-    } else {
-      // the next stage's codes (loaded a stage ago) into place, the one
-      // after it on its way
-      c0 = n0;
-      c1 = n1;
-      s0 = ns0;
-      z0 = nz0;
-      s1 = ns1;
-      z1 = nz1;
-      if (st + 2 < nst) fetch_codes(kn + kStage, n0, n1, ns0, nz0, ns1, nz1);
-    }
-    const bool in_n = interior(kn);
-    // buffer nxt was last read in step st - 1, before the barrier that ended it
-    if (more) {
-      if constexpr (kDirect) {
-        if (in_n) fetch_x(kn, nxt);
+  if constexpr (kDirect) {
+    // Everything straight into LDS.  A stage's last token block needs only
+    // fragments already in registers, so the barrier stands before it: behind
+    // it the stage's buffer takes the stage after the next, one load after
+    // each product, which then has almost a whole step to land, and the next
+    // stage's first fragments are read beside the block's products, so no
+    // wave waits for LDS at a stage's start.
+    // (W_hat) wave w's load q covers tile rows 8 (4 w + q) .. + 7 (1 KB): lane
+    // l fills slot l % 8 of row l / 8 of it with chunk (l % 8) ^ (row % 8).
+    // A row past n repeats row n - 1: it feeds only outputs never stored.
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
+    auto load_w = [&](int64_t k0, int buf, int q) {
+      const int r0 = 8 * (4 * uwave + q);
+      const int64_t j0 = J0 + r0 < a.n ? J0 + r0 : a.n - 1, left = a.n - 1 - j0;
+      const int lr = lane >> 3;
+      const uint32_t row = left >= 7 ? lr : (lr < (int)left ? lr : (int)left);
+      load_to_lds16(a.Wh + j0 * a.mw + k0, 2 * (row * (uint32_t)a.mw + 8 * ((lane & 7) ^ lr)),
+                    sA[buf] + r0 * kStage);
+    };
+    // (X) wave w's load q covers tile rows kRowsPer (4 w + q) .. (1 KB); lane l
+    // fills 16-byte slot l % kSlots of row l / kSlots of it, i.e. the 8 tokens
+    // of half (l % 2) of the swizzled block (l % kSlots) / 2.  Tokens past the
+    // last one (whole slots: T % 8 == 0) repeat the row's first ones; nothing
+    // of theirs is stored.
+    auto load_x = [&](int64_t k0, int buf, int q) {
+      const int r0 = kRowsPer * (4 * uwave + q), r = r0 + lane / kSlots;
+      const int u = ((lane % kSlots) >> 1) ^ xswz(r);
+      const int64_t t = T0 + 16 * u + 8 * (lane & 1);
+      if (!a.perm && a.ldx < (1 << 28)) {
+        load_to_lds16(a.X + (k0 + r0) * a.ldx,
+                      2 * ((uint32_t)(lane / kSlots) * (uint32_t)a.ldx + (uint32_t)(t < a.T ? t : 0)),
+                      sB[buf] + r0 * kTile);
       } else {
-        fetch_xv(kn);
+        const int64_t row =
+            !a.perm ? k0 + r : (prow[q] < 0 ? 0 : (prow[q] >= a.m ? a.m - 1 : prow[q]));
+        load_to_lds16_at(a.X + row * a.ldx + (t < a.T ? t : 0), sB[buf] + r0 * kTile);
       }
-    }
-    if constexpr (kDirect) {
-      if (st + 2 < nst) rows_for(kn + kStage);
-    }
-    compute(cur, nxt, kn, more);
-    if (more) {
-      if constexpr (!kDirect) {
-        store_xv(nxt);
-        if (!kPre && !in_n) mask_tail(kn, nxt);
-      } else if (!in_n) {
-        fetch_xv(kn);
-        store_xv(nxt);
+    };
+    auto stage_in = [&](int64_t st) {   // a whole stage at once
+      const int64_t k0 = st * kStage;
+      const int buf = (int)(st & 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) load_w(k0, buf, q);
+      if (interior(k0)) {
+        rows_for(k0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load_x(k0, buf, q);
+      } else {
+        fetch_xv(k0);
+        store_xv(buf);
       }
-    }
-    // (also keeps the compiler from waiting for this step's code loads at
-    // the top of the next step: it cannot pair their conditions)
+    };
+    h8 fa[NX], fb;
+    auto load_a = [&](int buf, int ks, int x) {
+      return *reinterpret_cast<const h8*>(sA[buf] +
+                                          aoff(16 * (NX * wr + x) + i16, 4 * ks + g16));
+    };
+    auto load_b = [&](int buf, int ks, int y) {
+      const int k0 = 32 * ks + 8 * g16, t0 = 16 * (NY * wc + y);
+      const s4 lo = read_tr<kTile>(sB[buf], k0, t0, i16);
+      const s4 hi = read_tr<kTile>(sB[buf], k0 + 4, t0, i16);
+      return __builtin_bit_cast(h8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    stage_in(0);
+    if (nst > 1) stage_in(1);
+    rows_for(2 * kStage);
     __builtin_amdgcn_s_waitcnt(0x0f70);
     __syncthreads();
+#pragma unroll
+    for (int x = 0; x < NX; ++x) fa[x] = load_a(0, 0, x);
+    fb = load_b(0, 0, 0);
+    for (int64_t st = 0; st < nst; ++st) {
+      const int cur = (int)(st & 1), nxt = cur ^ 1;
+      const int64_t k2 = (st + 2) * kStage;
+      const bool more2 = st + 2 < nst, in2 = interior(k2);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+        for (int y = 0; y < NY; ++y) {
+          const h8 fbc = fb;
+          const bool last = ks == 1 && y + 1 == NY;
+          if (last) {
+            __builtin_amdgcn_s_waitcnt(0x0f70);
+            __syncthreads();   // this stage is read, the next one in LDS
+            fb = load_b(nxt, 0, 0);
+          } else {
+            fb = y + 1 < NY ? load_b(cur, ks, y + 1) : load_b(cur, 1, 0);
+          }
+#pragma unroll
+          for (int x = 0; x < NX; ++x) {
+            acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[x], fbc, acc[x][y], 0, 0, 0);
+            if (y + 1 == NY) fa[x] = ks == 0 ? load_a(cur, 1, x) : load_a(nxt, 0, x);
+            if (last && more2) {
+              if constexpr (NX == 8) {
+                if (x < 4) load_w(k2, cur, x);
+                if (x >= 4 && in2) load_x(k2, cur, x - 4);
+              } else {
+                load_w(k2, cur, x);
+                if (in2) load_x(k2, cur, x);
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+      if (more2) {
+        if (!in2) {
+          fetch_xv(k2);
+          store_xv(cur);
+        }
+        rows_for(k2 + kStage);
+      }
+    }
+  } else {
+    // Stage st computes from buffer st % 2 while the activations (and W_hat)
+    // of stage st + 1 load straight into the other buffer, or its codes are
+    // dequantized into it beside the products.  vmcnt(0) before each barrier:
+    // the direct loads have landed in LDS.
+    if constexpr (kPre) {
+      fetch_w(0, 0);
+    } else {
+      fetch_codes(0, c0, c1, s0, z0, s1, z1);
+    }
+    fetch_xv(0);
+    store_xv(0);
+    if constexpr (!kPre) {
+      dequant_all(0, 0);
+      if (nst > 1) fetch_codes(kStage, n0, n1, ns0, nz0, ns1, nz1);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    __syncthreads();
+    for (int64_t st = 0; st < nst; ++st) {
+      const int cur = (int)(st & 1), nxt = cur ^ 1;
+      const int64_t kn = (st + 1) * kStage;
+      const bool more = st + 1 < nst;
+      if constexpr (kPre) {
+        if (more) fetch_w(kn, nxt);
+      } else {
+        // the next stage's codes (loaded a stage ago) into place, the one
+        // after it on its way
+        c0 = n0;
+        c1 = n1;
+        s0 = ns0;
+        z0 = nz0;
+        s1 = ns1;
+        z1 = nz1;
+        if (st + 2 < nst) fetch_codes(kn + kStage, n0, n1, ns0, nz0, ns1, nz1);
+      }
+      const bool in_n = interior(kn);
+      // buffer nxt was last read in step st - 1, before the barrier that ended it
+      if (more) fetch_xv(kn);
+      compute(cur, nxt, kn, more);
+      if (more) {
+        store_xv(nxt);
+        if (!kPre && !in_n) mask_tail(kn, nxt);
+      }
+      // (also keeps the compiler from waiting for this step's code loads at
+      // the top of the next step: it cannot pair their conditions)
+      __builtin_amdgcn_s_waitcnt(0x0f70);
+      __syncthreads();
+    }
   }
 
   // lane l holds D[4 (l / 16) + r][l % 16] of each 16x16 tile
