@@ -39,7 +39,7 @@ namespace {
 constexpr int kBS = kDecodeBlock;                 // rows per serial block
 constexpr int kGR = 4;                            // rows per serial group (one MFMA k-step)
 constexpr int kGBuf = kGR * 64;                   // group exchange buffer: 4 rows x 64 paths
-constexpr int kWaveLds = (kGBuf + kDecodeTile) * (int)sizeof(double);   // LDS bytes per wave
+constexpr int kWaveLds = (kGBuf + kDecodeTile + kBS) * (int)sizeof(double);   // LDS bytes per wave
 constexpr int kSeg = kBS;                         // code bytes per (block, lane)
 constexpr int kBlockCodes = 64 * kSeg;            // code bytes per (wave, block)
 static_assert(kBS == 32, "the block is eight 4-row MFMA steps and one 32-byte code segment");
@@ -55,6 +55,11 @@ static_assert(kBS % kGR == 0 && kBS / kGR <= 8, "a lane packs one code byte per 
 // them together hold less than 2^-55 of the probability mass, below the
 // rounding of the running sums, so the draw is that of the full box.
 constexpr double kLogCut = 45.0;
+
+// Above this gap (over kLogCut by more than the roundings on either way to
+// it) between the log-weights of the nearest box point and of its nearest
+// neighbour, the draw is the nearest point whatever the uniform is.
+constexpr double kSureCut = 46.0;
 
 constexpr double kTwo52 = 4503599627370496.0;   // 2^52
 constexpr int kTwo52Hi = 0x43300000;            // high word of 2^52 + x, 0 <= x < 2^32
@@ -104,6 +109,41 @@ __device__ __forceinline__ int klein_pick(double c, double kappa, double u, int 
     r *= q2;
   }
   return (int)hi;
+}
+
+// The same draw for most lanes from float32 weights.  With t = c - vs the
+// weight of vs + j is exp(-kappa j (j - 2 t)), so three exponentials give the
+// five points vs - 2 .. vs + 2; from kappa = 4 on the points beyond weigh less
+// than e^-24 together.  The exponents are formed in fp64 and rounded once, so
+// a weight is off by its exponent (below 20 where the weight matters at all)
+// times 2^-24 and the hardware exponential's last bit, the running sums by
+// less than 2^-17 of the total.  A uniform within 2^-15 of it of a running sum
+// decides nothing (*sure false: the caller evaluates klein_pick), any other
+// falls as it does in fp64.
+__device__ __forceinline__ int klein_fast(double c, int vs, double kappa, float u, int qmax,
+                                          bool* sure) {
+  const double t = c - (double)vs, k2 = kappa * 1.4426950408889634;   // log2(e)
+  const float wm = __builtin_amdgcn_exp2f(-(float)(k2 * fma(2.0, t, 1.0)));
+  const float wp = __builtin_amdgcn_exp2f(-(float)(k2 * fma(-2.0, t, 1.0)));
+  const float q2 = __builtin_amdgcn_exp2f(-2.0f * (float)k2);
+  const float b0 = vs >= 2 ? wm * wm * q2 : 0.0f;
+  const float b1 = b0 + (vs >= 1 ? wm : 0.0f);
+  const float b2 = b1 + 1.0f;
+  const float b3 = b2 + (vs < qmax ? wp : 0.0f);
+  const float total = b3 + (vs < qmax - 1 ? wp * wp * q2 : 0.0f);
+  const float thr = u * total;
+  const float near = fminf(fminf(fabsf(thr - b0), fabsf(thr - b1)),
+                           fminf(fabsf(thr - b2), fabsf(thr - b3)));
+  *sure = near > 0x1p-15f * total && kappa >= 4.0;
+  return vs - 2 + (thr >= b0) + (thr >= b1) + (thr >= b2) + (thr >= b3);
+}
+
+// 1 / d to the last bit or two: hardware estimate, two Newton steps.
+__device__ __forceinline__ double recip(double d) {
+  double y = __builtin_amdgcn_rcp(d);
+#pragma unroll
+  for (int it = 0; it < 2; ++it) y = fma(fma(-d, y, 1.0), y, y);
+  return y;
 }
 
 // All lanes of the wave have finished their LDS / global accesses before any
@@ -477,7 +517,9 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
 
   double* const sG = sZ;            // [4][64]: a group's z or e values by (row, path)
   double* const sD = sZ + kGBuf;    // sD[r * 32 + c] = R[i0 + c][i0 + r], c <= r
+  double* const sI = sD + kDecodeTile;   // sI[r] = 1 / R[i0 + r][i0 + r]
 
+  const KleinLane kw = klein_lane((uint32_t)j, kk, (uint32_t)d.seed);
   double resid = 0.0;
   uint32_t rk = 0;   // position in the digit ring (int8 update)
   for (int64_t b = nb - 1; b >= 0; --b) {
@@ -517,13 +559,27 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
     wave_sync();   // the diagonal tile is in LDS
 
     // ---- serial steps, one path per lane, in groups of four rows from the
-    // top.  A group's rows sit in one slot (a, r) of the accumulator (rows
+    // top.  They are bound by the vector ALU and by their own dependency
+    // chain, so a row costs no more than it must: the centre is z times
+    // 1 / R_ii (once per block and row) and 1 / s (once per block), with one
+    // correction step that restores the quotient's rounding; a Klein draw
+    // takes float32 weights (three hardware exponentials) and goes through
+    // fp64 ones only where the uniform falls next to a running sum, none where
+    // the nearest point is the certain draw; Philox's first two rounds are
+    // mostly constants of the lane (4096 x 4096, 17 paths a column: the kernel
+    // 7.8 ms, 10.5 with fp64 weights, a division and all of Philox per row).
+    // A group's rows sit in one slot (a, r) of the accumulator (rows
     // 16 a + 4 r + l / 16); they reach their lanes through LDS, update each
     // other in registers, and update the rows below with one MFMA step
     // (K = 4) on the accumulator: R[., group] E[group] ----
-    uint64_t wcode[kGR] = {0, 0, 0, 0};   // byte g of wcode[k]: code of row kGR g + k
-    double s_blk = 0.0;
-    if constexpr (kUniS) s_blk = (double)Sj[G == 1 ? 0u : (uint32_t)i0 / (uint32_t)g];
+    // byte g of wlo[k] (g < 4), byte g - 4 of whi[k]: code of row kGR g + k
+    uint32_t wlo[kGR] = {0, 0, 0, 0}, whi[kGR] = {0, 0, 0, 0};
+    double s_blk = 0.0, inv_s = 0.0;
+    if constexpr (kUniS) {
+      s_blk = (double)Sj[G == 1 ? 0u : (uint32_t)i0 / (uint32_t)g];
+      inv_s = recip(s_blk);
+      if (lane < kBS) sI[lane] = lane < bl ? recip(sD[lane * (kBS + 1)]) : 0.0;
+    }
     for (int g4 = (bl - 1) / kGR; g4 >= 0; --g4) {
       const int r0 = kGR * g4;
       double* const gslot = sG + (lane >> 4) * 64 + (lane & 15);
@@ -537,7 +593,7 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
 #undef OJBKQ_PUT_GROUP
       }
       wave_sync();
-      double z[kGR], u[kGR], sr[kGR], rb[kGR];
+      double z[kGR], sr[kGR], rb[kGR], inv[kGR];
 #pragma unroll
       for (int k = 0; k < kGR; ++k) {
         z[k] = -sG[k * 64 + lane];
@@ -550,20 +606,44 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
           sr[k] = (double)Sj[d.gidx ? (uint32_t)d.gidx[row] : row / (uint32_t)g];
         }
         rb[k] = sD[(r0 + k) * (kBS + 1)] * sr[k];   // Rbar_ii
-        u[k] = (kk != 0) ? klein_uniform(d.seed, (uint32_t)(i0 + r0 + k), (uint32_t)j, kk) : 0.0;
+        inv[k] = kUniS ? sI[r0 + k] * inv_s : recip(rb[k]);
       }
+      // the group's random words : counter (row, column, path, 0)
+      uint32_t x0[kGR], x1[kGR];
+#pragma unroll
+      for (int k = 0; k < kGR; ++k)
+        klein_words(kw, (uint32_t)(i0 + r0 + k), (uint32_t)d.seed, (uint32_t)(d.seed >> 32), x0[k],
+                    x1[k]);
       double e[kGR];
 #pragma unroll
       for (int k = kGR - 1; k >= 0; --k) {
         e[k] = 0.0;
         if (r0 + k < bl && valid) {
-          const double c = z[k] / rb[k];   // centre of row i0 + r0 + k
-          const int q = (kk == 0) ? (int)nearest_box_point(c, qmax)
-                                  : klein_pick(c, alpha_j * (rb[k] * rb[k]), u[k], qmax);
-          const double dq = rb[k] * ((double)q - c);
+          // centre of row i0 + r0 + k: z / rb, the remainder of the first
+          // product divided once more
+          double c = z[k] * inv[k];
+          c = fma(fma(-c, rb[k], z[k]), inv[k], c);
+          const double cc = fmin(fmax(c, 0.0), (double)qmax);
+          double q = rint(cc);   // the nearest box point
+          if (kk != 0) {
+            const double kappa = alpha_j * (rb[k] * rb[k]);
+            // (distance to the nearest neighbour in the box)^2 - (to q)^2
+            const double gap = fma(2.0, fabs(c - cc), fma(-2.0, fabs(cc - q), 1.0));
+            if (!(kappa * gap > kSureCut)) {
+              bool sure;
+              int v = klein_fast(c, (int)q, kappa, (float)x0[k] * 0x1p-32f, qmax, &sure);
+              if (!sure) v = klein_pick(c, kappa, uniform53(x0[k], x1[k]), qmax);
+              q = (double)v;
+            }
+          }
+          const double dq = rb[k] * (q - c);
           resid += dq * dq;
-          e[k] = sr[k] * (double)q;
-          wcode[k] |= (uint64_t)q << (8 * g4);
+          e[k] = sr[k] * q;
+          const uint32_t byte = (uint32_t)(int)q << (8 * (g4 & 3));
+          if (g4 < 4)
+            wlo[k] |= byte;
+          else
+            whi[k] |= byte;
         }
 #pragma unroll
         for (int k2 = 0; k2 < k; ++k2) z[k2] -= sD[(r0 + k) * kBS + r0 + k2] * e[k];
@@ -587,10 +667,8 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
       wave_sync();   // the e reads are done before the next group's writes
     }
     uint8_t* seg = cw + b * kBlockCodes + lane * kSeg;
-    *reinterpret_cast<uint4*>(seg) = make_uint4((uint32_t)wcode[0], (uint32_t)(wcode[0] >> 32),
-                                                (uint32_t)wcode[1], (uint32_t)(wcode[1] >> 32));
-    *reinterpret_cast<uint4*>(seg + 16) = make_uint4((uint32_t)wcode[2], (uint32_t)(wcode[2] >> 32),
-                                                     (uint32_t)wcode[3], (uint32_t)(wcode[3] >> 32));
+    *reinterpret_cast<uint4*>(seg) = make_uint4(wlo[0], whi[0], wlo[1], whi[1]);
+    *reinterpret_cast<uint4*>(seg + 16) = make_uint4(wlo[2], whi[2], wlo[3], whi[3]);
     wave_sync();   // codes visible to the later update loads; LDS reads done
   }
   if (valid) d.presid[p] = resid;

@@ -18,23 +18,46 @@ __device__ __forceinline__ d4 mfma_f64(double a, double b, d4 c) {
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11): ten rounds of two
-// 32x32->64-bit products on a 128-bit counter, key bumped by the two Weyl
-// constants between rounds.
-struct Philox4 {
-  uint32_t x0, x1, x2, x3;
-};
+// 32x32->64-bit products (one v_mad_u64_u32 each) on a 128-bit counter, key
+// bumped by the two Weyl constants between rounds.
 
-__device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2,
-                                                 uint32_t c3, uint32_t k0, uint32_t k1) {
+// Uniform double in [0, 1) for the Klein draw of (row i, column j, candidate
+// k): counter (i, j, k, 0), key (seed lo, seed hi), 53 bits from the first
+// two words (27 high bits of x0, 26 high bits of x1).
+__device__ __forceinline__ double uniform53(uint32_t x0, uint32_t x1) {
+  const double hi = (double)(x0 >> 5);
+  const double lo = (double)(x1 >> 6);
+  return (hi * 67108864.0 + lo) * (1.0 / 9007199254740992.0);
+}
+
+// philox4x32_10 of those counters for a lane that walks the rows i: the first
+// round's product with k and the second's with its result are the same for
+// every row.
+struct KleinLane {
+  uint32_t lo1;        // low word of kM1 k
+  uint32_t hi2, lo2;   // kM0 c0 of the second round
+};
+__device__ __forceinline__ KleinLane klein_lane(uint32_t j, uint32_t k, uint32_t k0) {
+  const uint64_t p1 = 0xCD9E8D57ull * k;
+  const uint64_t p0 = 0xD2511F53ull * ((uint32_t)(p1 >> 32) ^ j ^ k0);
+  return KleinLane{(uint32_t)p1, (uint32_t)(p0 >> 32), (uint32_t)p0};
+}
+__device__ __forceinline__ void klein_words(const KleinLane& w, uint32_t i, uint32_t k0,
+                                            uint32_t k1, uint32_t& x0, uint32_t& x1) {
   constexpr uint32_t kM0 = 0xD2511F53u, kM1 = 0xCD9E8D57u;
   constexpr uint32_t kW0 = 0x9E3779B9u, kW1 = 0xBB67AE85u;
+  // rounds one and two (the row's own words are the same for every lane)
+  const uint64_t pi = (uint64_t)kM0 * i;
+  const uint32_t c2i = (uint32_t)(pi >> 32) ^ k1;
+  k0 += kW0;
+  k1 += kW1;
+  const uint64_t q1 = (uint64_t)kM1 * c2i;
+  uint32_t c0 = (uint32_t)(q1 >> 32) ^ w.lo1 ^ k0, c1 = (uint32_t)q1;
+  uint32_t c2 = w.hi2 ^ (uint32_t)pi ^ k1, c3 = w.lo2;
 #pragma unroll
-  for (int round = 0; round < 10; ++round) {
-    if (round) {
-      k0 += kW0;
-      k1 += kW1;
-    }
-    // one v_mad_u64_u32 per 32 x 32 -> 64-bit product (both halves at once)
+  for (int round = 2; round < 10; ++round) {
+    k0 += kW0;
+    k1 += kW1;
     const uint64_t p0 = (uint64_t)kM0 * c0, p1 = (uint64_t)kM1 * c2;
     const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
     const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
@@ -43,18 +66,8 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
     c2 = n2;
     c3 = (uint32_t)p0;
   }
-  return Philox4{c0, c1, c2, c3};
-}
-
-// Uniform double in [0, 1) for the Klein draw of (row i, column j, candidate
-// k): counter (i, j, k, 0), key (seed lo, seed hi), 53 bits from the first
-// two words (27 high bits of x0, 26 high bits of x1).
-__device__ __forceinline__ double klein_uniform(uint64_t seed, uint32_t i, uint32_t j,
-                                                uint32_t k) {
-  const Philox4 r = philox4x32_10(i, j, k, 0u, (uint32_t)seed, (uint32_t)(seed >> 32));
-  const double hi = (double)(r.x0 >> 5);
-  const double lo = (double)(r.x1 >> 6);
-  return (hi * 67108864.0 + lo) * (1.0 / 9007199254740992.0);
+  x0 = c0;
+  x1 = c1;
 }
 
 typedef __attribute__((address_space(3))) void lds_void;
