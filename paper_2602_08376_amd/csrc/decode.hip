@@ -279,11 +279,13 @@ __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
 //
 // Every wave of the workgroup walks the same blocks, so a unit's digit tiles
 // (up to 28 KB) are loaded once per workgroup, straight into an LDS ring of
-// two units: the next unit's tiles stream in while the current one's products
-// run, with one barrier per unit.  The ring position `rk` runs on across the
-// blocks, so a block's first unit goes to the slot its predecessor's last
-// unit did not use (every wave finished reading that one before the last
-// barrier).
+// two units, and each wave's codes straight into an LDS area of its own; the
+// next unit's load while the current one's products run, with one barrier
+// per unit.  A block's units go from the last pairs down to the newest, so
+// that the stream runs on across the serial steps: at a block's last unit the
+// first one of the next block is loaded (its codes too, unless they are the
+// ones about to be decided), and the ring position rk runs on across the
+// blocks.
 //
 // A unit runs over items (e, h): digit pair e, row half h.  The products of
 // an item are issued one at a time, each followed by one share of the fp64
@@ -292,48 +294,69 @@ __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
 // vector ALU work side by side; the next item's digits are read from LDS
 // while it runs.  A pair slot outside the unit (the first unit of a block
 // that starts at its second pair, the last one of a block that ends at its
-// first) reads its digits from a tile of zeros and its codes from a decided
-// pair, so no item branches.  Each wave's codes and scales of the next unit
-// are loaded in the last digit pair, whose second digit does not exist, so
-// its int32 sums free the registers.
+// first) reads its digits from a tile of zeros, so no item branches.  Loading
+// the codes into registers in the unit's last digit pair left their latency
+// bare: 590 ms at 8192 x 28672, 17 paths a column, now 563; 13824 x 5120, 33
+// paths: 71.5, now 69.6 ms.
 constexpr int kUnitBytes = 2 * kDigitTileBytes;   // one LDS ring slot
 constexpr int kRingBytes = 2 * kUnitBytes + kDigitTileBytes;   // two slots and a zero tile
+// LDS of the int8 form: per wave the group buffer and reciprocals, and the
+// codes of a unit of two pairs and three tiles; per workgroup two diagonal
+// tiles (in turn) and the ring
+constexpr int kWaveLdsI8 = (kGBuf + kBS) * (int)sizeof(double);
+constexpr int kWaveCodes = 2 * 3 * 1024;
+constexpr int kDiagBytes = kDecodeTile * (int)sizeof(double);
+inline size_t decode_lds_i8(int waves) {
+  return (size_t)waves * (kWaveLdsI8 + kWaveCodes) + 2 * kDiagBytes + kRingBytes;
+}
+
+// What the waves have under way for the next unit of the stream.
+struct LazyStream {
+  uint32_t rk = 0;        // its position in the digit ring
+  bool digits = false;    // its digit tiles are loading
+  bool codes = false;     // this wave's codes for it are loading
+};
 
 template <int NT, int kU>
 __device__ __forceinline__ void lazy_units_i8(const DecodeDesc& d, int64_t nb2, int64_t b,
                                               const uint8_t* cw, const uint32_t (&so)[NT],
                                               d4 (&acc)[2][NT], int lane, uint8_t* ring,
-                                              uint32_t& rk) {
+                                              uint8_t* sC, LazyStream& ls) {
   const int64_t c0 = (b + 1) / 2;
-  const uint8_t* const tile_c0 = d.R8 + decode_digit_tile(nb2, b, c0) * kDigitTileBytes;
+  const int64_t u_lo = c0 / kU * kU, u_hi = (nb2 - 1) / kU * kU;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int waves = d.threads >> 6;
-  // the digit tiles of unit u's pairs into ring slot `slot`, 1 KB (one
-  // direct-to-LDS load of 16 bytes per lane) at a time, dealt to the waves
-  auto issue = [&](int64_t u, uint32_t slot) {
-    const int64_t pa = u > c0 ? u : c0, pb = u + kU < nb2 ? u + kU : nb2;
+  // the digit tiles of unit u's pairs of block bb into ring slot `slot`, 1 KB
+  // (one direct-to-LDS load of 16 bytes per lane) at a time, dealt to the waves
+  auto issue_digits = [&](int64_t bb, int64_t u, uint32_t slot) {
+    const int64_t cb = (bb + 1) / 2;
+    const int64_t pa = u > cb ? u : cb, pb = u + kU < nb2 ? u + kU : nb2;
     const int nblk = (int)(pb - pa) * (kDigitTileBytes / 1024);
-    const uint8_t* src = tile_c0 + (pa - c0) * kDigitTileBytes;
+    const uint8_t* src = d.R8 + decode_digit_tile(nb2, bb, pa) * kDigitTileBytes;
     uint8_t* dst = ring + (slot & 1) * kUnitBytes + (pa - u) * kDigitTileBytes;
     for (int q = wave; q < nblk; q += waves) load_to_lds16(src + q * 1024, 16 * lane, dst + q * 1024);
   };
-  // this lane's 16 code bytes of pair c for tile t (block 2c + lane / 32,
-  // path 16 t + lane % 16, bytes 16 ((lane / 16) % 2) ..), pairs past the
-  // last clamped to it; the scales of the unit's group
-  const uint8_t* const cb =
-      cw + (lane >> 5) * kBlockCodes + (lane & 15) * kSeg + 16 * ((lane >> 4) & 1);
-  auto load_codes = [&](int64_t c, v4i (&Bs)[NT]) {
-    c = c < nb2 ? c : nb2 - 1;
+  // this lane's 16 code bytes of each pair and tile (block 2c + lane / 32,
+  // path 16 t + lane % 16, bytes 16 ((lane / 16) % 2) ..) into the wave's own
+  // LDS area, pairs past the last one clamped to it
+  const uint32_t cb_off = (uint32_t)((lane >> 5) * kBlockCodes + (lane & 15) * kSeg +
+                                     16 * ((lane >> 4) & 1));
+  auto issue_codes = [&](int64_t u) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-      Bs[t] = *reinterpret_cast<const v4i*>(cb + 2 * c * kBlockCodes + t * 16 * kSeg);
+    for (int s = 0; s < kU; ++s) {
+      const int64_t c = u + s < nb2 ? u + s : nb2 - 1;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        load_to_lds16(cw + 2 * c * kBlockCodes + t * 16 * kSeg, cb_off, sC + (s * NT + t) * 1024);
+    }
   };
-  auto load_scales = [&](int64_t u, float (&sc)[NT]) {
-    const int64_t uc = u < nb2 ? u : nb2 - 1;
-    const uint32_t grp = d.G == 1 ? 0u : (uint32_t)((64 * uc) / d.g);
+  auto load_scales = [&](uint32_t grp, float (&sc)[NT]) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) sc[t] = load_scale(d.S + (so[t] + grp));
   };
+  // group of unit u and its first row's place in it (m < 2^20: 32 bits)
+  uint32_t grp = d.G == 1 ? 0u : (uint32_t)(64 * u_hi) / (uint32_t)d.g;
+  int32_t in_grp = (int32_t)(64 * u_hi) - (int32_t)(grp * (uint32_t)d.g);
   constexpr int kE = (kDecodeDigits + 1) / 2;   // digit pairs
   static_assert(kDecodeDigits % 2 == 1 && kE >= 3, "the last digit pair has one digit");
   const uint8_t* const zero = ring + 2 * kUnitBytes + 16 * lane;
@@ -357,7 +380,7 @@ __device__ __forceinline__ void lazy_units_i8(const DecodeDesc& d, int64_t nb2, 
     constexpr int kPer = (kF + kM - 1) / kM;          // flush elements per product
     auto flush_el = [&](int f) {
       const int t = f / 4, r = f % 4;
-      const int v = kTwoF ? a1[hf][t][r] * 128 + a2[hf][t][r] : a1[hf][t][r] * 128;
+      const int v = kTwoF ? a1[hf][t][r] * 128 + a2[hf][t][r] : a1[hf][t][r];
       acc[hf][t][r] = fma(m[t], (double)v, acc[hf][t][r]);
     };
 #pragma unroll
@@ -375,26 +398,42 @@ __device__ __forceinline__ void lazy_units_i8(const DecodeDesc& d, int64_t nb2, 
   const std::true_type two{};
   const std::false_type one{};
 
-  int64_t u = c0 / kU * kU;
-  v4i Bq[kU][NT], Bn[kU][NT];
+  v4i Bq[kU][NT];
   float sc[NT], scn[NT];
-#pragma unroll
-  for (int s = 0; s < kU; ++s) load_codes(u + s, Bn[s]);
-  load_scales(u, scn);
-  issue(u, rk);
-  for (; u < nb2; u += kU, ++rk) {
+  if (!ls.digits) issue_digits(b, u_hi, ls.rk);
+  if (!ls.codes) issue_codes(u_hi);
+  load_scales(grp, scn);
+  for (int64_t u = u_hi; u >= u_lo; u -= kU, ++ls.rk) {
+    const uint32_t rk = ls.rk;
     const int64_t pa = u > c0 ? u : c0, pb = u + kU < nb2 ? u + kU : nb2;
-    // this unit's tiles, codes and scales have landed, and every wave is
-    // done with the other ring slot
+    // this wave's loads have landed (its codes are its own: read before the
+    // barrier), then every wave's, and every wave is done with the other ring
+    // slot
     wait_loads();
-    __syncthreads();
 #pragma unroll
     for (int s = 0; s < kU; ++s)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) Bq[s][t] = Bn[s][t];
+      for (int t = 0; t < NT; ++t)
+        Bq[s][t] = *reinterpret_cast<const v4i*>(sC + (s * NT + t) * 1024 + 16 * lane);
+    __syncthreads();
 #pragma unroll
     for (int t = 0; t < NT; ++t) sc[t] = scn[t];
-    if (pb < nb2) issue(pb, rk + 1);
+    // the next unit: of this block, or the first one of the next block, whose
+    // codes are decided already unless they include this block's
+    const bool more = u > u_lo;
+    ls.digits = more || b > 0;
+    if (ls.digits) issue_digits(more ? b : b - 1, more ? u - kU : u_hi, rk + 1);
+    ls.codes = more || (b > 0 && b / 2 < u_hi);
+    if (more) {
+      if (d.G != 1) {
+        in_grp -= 64 * kU;
+        if (in_grp < 0) {
+          in_grp += (int32_t)d.g;
+          --grp;
+        }
+      }
+      load_scales(grp, scn);
+    }
     // lane-relative LDS tiles of the unit's pair slots (zeros outside it)
     const uint8_t* tile[kU];
 #pragma unroll
@@ -414,13 +453,15 @@ __device__ __forceinline__ void lazy_units_i8(const DecodeDesc& d, int64_t nb2, 
     };
     auto set_mult = [&](int e) {
 #pragma unroll
-      for (int t = 0; t < NT; ++t) mult[t] = ldexp((double)sc[t], -13 - 14 * e);
+      for (int t = 0; t < NT; ++t)
+        mult[t] = ldexp((double)sc[t], (2 * e + 1 < kDecodeDigits ? -13 : -6) - 14 * e);
     };
     v4i Ac[kU][2], An[kU][2];
     load_a(0, 0, Ac);
     // e = 0: half 0 beside the previous unit's last half 1, half 1 beside half 0
     load_a(0, 1, An);
     item(0, Ac, Bq, two, 1, mprev, one);
+    if (ls.codes) issue_codes(more ? u - kU : u_hi);   // this unit's are in registers
     set_mult(0);
     load_a(1, 0, Ac);
     item(1, An, Bq, two, 0, mult, two);
@@ -432,11 +473,8 @@ __device__ __forceinline__ void lazy_units_i8(const DecodeDesc& d, int64_t nb2, 
       load_a(e + 1, 0, Ac);
       item(1, An, Bq, two, 0, mult, two);
     }
-    // e = kE - 1 (one digit); the next unit's codes and scales meanwhile
+    // e = kE - 1 (one digit)
     load_a(kE - 1, 1, An);
-#pragma unroll
-    for (int s = 0; s < kU; ++s) load_codes(u + kU + s, Bn[s]);
-    load_scales(u + kU, scn);
     item(0, Ac, Bq, one, 1, mult, two);
     set_mult(kE - 1);
     item(1, An, Bq, one, 0, mult, one);
@@ -448,16 +486,20 @@ __device__ __forceinline__ void lazy_units_i8(const DecodeDesc& d, int64_t nb2, 
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      acc[1][t][r] = fma(mprev[t], (double)(a1[1][t][r] * 128), acc[1][t][r]);
+      acc[1][t][r] = fma(mprev[t], (double)a1[1][t][r], acc[1][t][r]);
 }
 
 template <int NT>
 __device__ __forceinline__ void lazy_update_i8(const DecodeDesc& d, int64_t nb, int64_t b,
                                                const uint8_t* cw, const uint32_t (&so)[NT],
                                                d4 (&acc)[2][NT], int lane, uint8_t* ring,
-                                               uint32_t& rk) {
+                                               uint8_t* sC, LazyStream& ls) {
   const int64_t nb2 = (nb + 1) / 2;
-  if ((b + 1) / 2 >= nb2) return;   // the same for every wave
+  if ((b + 1) / 2 >= nb2) {   // no decided pair (the same for every wave)
+    wait_loads();
+    __syncthreads();          // the diagonal tile is in LDS
+    return;
+  }
   // into units of 2^rexp of this lane's rows 32 b + 16 a + lane / 16 + 4 r
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -470,9 +512,9 @@ __device__ __forceinline__ void lazy_update_i8(const DecodeDesc& d, int64_t nb, 
     }
   // two pairs per unit unless a scale group ends after one
   if (d.G == 1 || d.g % 128 == 0)
-    lazy_units_i8<NT, 2>(d, nb2, b, cw, so, acc, lane, ring, rk);
+    lazy_units_i8<NT, 2>(d, nb2, b, cw, so, acc, lane, ring, sC, ls);
   else
-    lazy_units_i8<NT, 1>(d, nb2, b, cw, so, acc, lane, ring, rk);
+    lazy_units_i8<NT, 1>(d, nb2, b, cw, so, acc, lane, ring, sC, ls);
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -486,10 +528,12 @@ __device__ __forceinline__ void lazy_update_i8(const DecodeDesc& d, int64_t nb, 
 
 // One wave's share of the decode: paths pbase .. pbase + npw - 1 (npw <= 64,
 // in NT = ceil(npw / 16) tiles), codes at cw, LDS buffer sZ of kWaveLds bytes;
-// with the int8 update, the workgroup's digit ring (kRingBytes) at ring.
+// with the int8 update kWaveLdsI8 bytes, the wave's kWaveCodes at sC, the
+// workgroup's two diagonal tiles at diag and its digit ring at ring.
 template <int NT, bool kUniS, bool kI8>
 __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, int npw,
-                                            uint8_t* cw, double* sZ, uint8_t* ring) {
+                                            uint8_t* cw, double* sZ, uint8_t* sC, double* diag,
+                                            uint8_t* ring) {
   const int lane = threadIdx.x & 63;
   const int64_t m = d.m, g = d.g, G = d.G;
   const int64_t kp1 = (int64_t)d.K + 1;
@@ -516,19 +560,27 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
   const float* const Spj = d.spos ? d.spos + j * (nb * kBS) : nullptr;
 
   double* const sG = sZ;            // [4][64]: a group's z or e values by (row, path)
-  double* const sD = sZ + kGBuf;    // sD[r * 32 + c] = R[i0 + c][i0 + r], c <= r
-  double* const sI = sD + kDecodeTile;   // sI[r] = 1 / R[i0 + r][i0 + r]
+  double* const sI = sZ + kGBuf;    // sI[r] = 1 / R[i0 + r][i0 + r]
 
   const KleinLane kw = klein_lane((uint32_t)j, kk, (uint32_t)d.seed);
   double resid = 0.0;
-  uint32_t rk = 0;   // position in the digit ring (int8 update)
+  LazyStream ls;   // (int8 update)
   for (int64_t b = nb - 1; b >= 0; --b) {
     const int64_t i0 = b * kBS;
     const int bl = (int)((m - i0) < kBS ? (m - i0) : kBS);
 
-    // ---- the block's diagonal tile to LDS (the previous block's reads
-    // ended at its last wave_sync) ----
-    {
+    // ---- the block's diagonal tile to LDS: sD[r * 32 + c] = R[i0 + c][i0 + r],
+    // c <= r.  One per wave (the previous block's reads ended at its last
+    // wave_sync), or with the int8 update one per workgroup, two in turn: the
+    // buffer was read two blocks ago, before the barriers of the block
+    // between; the barriers of this block's update publish it ----
+    double* const sD = kI8 ? diag + (b & 1) * kDecodeTile : sI + kBS;
+    if constexpr (kI8) {
+      const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+      for (int q = wave; q < kDiagBytes / 1024; q += d.threads >> 6)
+        load_to_lds16(d.F + b * kDecodeTile + q * 128, 16 * lane,
+                      diag + (b & 1) * kDecodeTile + q * 128);
+    } else {
       const double* Dt = d.F + b * kDecodeTile + 2 * lane;
 #pragma unroll
       for (int q = 0; q < kDecodeTile / 128; ++q)
@@ -552,7 +604,7 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
         }
     }
     if constexpr (kI8) {
-      if (b + 1 < nb) lazy_update_i8<NT>(d, nb, b, cw, so, acc, lane, ring, rk);
+      lazy_update_i8<NT>(d, nb, b, cw, so, acc, lane, ring, sC, ls);
     } else {
       if (b + 1 < nb) lazy_update<NT, kUniS>(d, nb, b, cw, so, sp, acc, lane);
     }
@@ -608,7 +660,7 @@ __device__ __forceinline__ void decode_wave(const DecodeDesc& d, int64_t pbase, 
         rb[k] = sD[(r0 + k) * (kBS + 1)] * sr[k];   // Rbar_ii
         inv[k] = kUniS ? sI[r0 + k] * inv_s : recip(rb[k]);
       }
-      // the group's random words : counter (row, column, path, 0)
+      // the group's random words: counter (row, column, path, 0)
       uint32_t x0[kGR], x1[kGR];
 #pragma unroll
       for (int k = 0; k < kGR; ++k)
@@ -695,8 +747,10 @@ __global__ __launch_bounds__(kDecodeMaxThreads) void decode_kernel(DecodeDesc d)
   const int npw = pbase < pend ? (int)(pend - pbase) : 0;
   uint8_t* cw =
       d.pcodes + ((int64_t)blockIdx.x * waves + wave) * decode_code_blocks(d.m) * kBlockCodes;
-  double* sZ = lds + wave * (kWaveLds / (int)sizeof(double));
-  uint8_t* ring = reinterpret_cast<uint8_t*>(lds) + waves * kWaveLds;
+  double* sZ = lds + wave * ((kI8 ? kWaveLdsI8 : kWaveLds) / (int)sizeof(double));
+  double* diag = lds + waves * (kWaveLdsI8 / (int)sizeof(double));
+  uint8_t* ring = reinterpret_cast<uint8_t*>(diag + 2 * kDecodeTile);
+  uint8_t* sC = ring + kRingBytes + wave * kWaveCodes;
   if constexpr (kI8) {
     // the ring's tile of zero digits (read after the first unit's barrier)
     for (int i = (int)threadIdx.x; i < kDigitTileBytes / 16; i += d.threads)
@@ -704,14 +758,14 @@ __global__ __launch_bounds__(kDecodeMaxThreads) void decode_kernel(DecodeDesc d)
   }
   switch ((npw + 15) / 16) {
     case 0:
-    case 1: decode_wave<1, kUniS, kI8>(d, pbase, npw, cw, sZ, ring); break;
-    case 2: decode_wave<2, kUniS, kI8>(d, pbase, npw, cw, sZ, ring); break;
-    case 3: decode_wave<3, kUniS, kI8>(d, pbase, npw, cw, sZ, ring); break;
+    case 1: decode_wave<1, kUniS, kI8>(d, pbase, npw, cw, sZ, sC, diag, ring); break;
+    case 2: decode_wave<2, kUniS, kI8>(d, pbase, npw, cw, sZ, sC, diag, ring); break;
+    case 3: decode_wave<3, kUniS, kI8>(d, pbase, npw, cw, sZ, sC, diag, ring); break;
     default:   // the int8 update's geometry gives a wave at most three tiles
       if constexpr (kI8)
-        decode_wave<3, kUniS, kI8>(d, pbase, npw, cw, sZ, ring);
+        decode_wave<3, kUniS, kI8>(d, pbase, npw, cw, sZ, sC, diag, ring);
       else
-        decode_wave<4, kUniS, kI8>(d, pbase, npw, cw, sZ, ring);
+        decode_wave<4, kUniS, kI8>(d, pbase, npw, cw, sZ, sC, diag, ring);
       break;
   }
 }
@@ -953,7 +1007,7 @@ hipError_t launch_decode(const DecodeDesc& d, hipStream_t stream) {
   geo.nwg = d.nwg;
   const bool uniform_scale = !d.gidx && !d.spos && (d.G == 1 || d.g % kBS == 0);
   const bool i8 = d.R8 != nullptr;
-  const size_t lds = (size_t)(d.threads / 64) * kWaveLds + (i8 ? kRingBytes : 0);
+  const size_t lds = i8 ? decode_lds_i8(d.threads / 64) : (size_t)(d.threads / 64) * kWaveLds;
   if (i8 && (!d.rexp || d.gidx || d.spos || d.bits > 7 || (d.G != 1 && d.g % 64 != 0) ||
              d.wg_paths > 3 * 16 * (int64_t)(d.threads / 64)))
     return hipErrorInvalidValue;

@@ -33,6 +33,9 @@ __device__ __forceinline__ double uniform53(uint32_t x0, uint32_t x1) {
 // philox4x32_10 of those counters for a lane that walks the rows i: the first
 // round's product with k and the second's with its result are the same for
 // every row.
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);   // one v_bitop3_b32
+}
 struct KleinLane {
   uint32_t lo1;        // low word of kM1 k
   uint32_t hi2, lo2;   // kM0 c0 of the second round
@@ -59,8 +62,8 @@ __device__ __forceinline__ void klein_words(const KleinLane& w, uint32_t i, uint
     k0 += kW0;
     k1 += kW1;
     const uint64_t p0 = (uint64_t)kM0 * c0, p1 = (uint64_t)kM1 * c2;
-    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+    const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+    const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
     c0 = n0;
     c1 = (uint32_t)p1;
     c2 = n2;
@@ -70,7 +73,11 @@ __device__ __forceinline__ void klein_words(const KleinLane& w, uint32_t i, uint
   x1 = c1;
 }
 
-typedef __attribute__((address_space(3))) void lds_void;
+// LDS address of a generic pointer into LDS: its low word (the shared
+// aperture is aligned to 4 GB).
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return (uint32_t)reinterpret_cast<uintptr_t>(p);
+}
 
 // 16 bytes per lane from global memory straight to LDS: lane i reads base +
 // off_i (base the same for every lane) and its bytes land at LDS address
@@ -79,18 +86,24 @@ typedef __attribute__((address_space(3))) void lds_void;
 // every LDS read after such a load as possibly out of order and wait for all
 // of them); a vmcnt(0) wait before the barrier that publishes the data covers
 // its completion.  The LDS address goes in M0, set by the compiler; one wait
-// state separates that write from the load reading it.
+// state separates that write from the load reading it.  A base that the
+// vector ALU wrote (readfirstlane, or readlane where the compiler keeps it in
+// a spilled lane) may be read by the load only five wait states later, and
+// the compiler, which does not see that the asm is a load, inserts none: the
+// load reads a copy that the scalar ALU makes (reads by it are interlocked),
+// which is the wait state for M0 as well.
 __device__ __forceinline__ void load_to_lds16(const void* base, uint32_t off, const void* lds) {
-  const uint32_t a = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(const lds_void*)lds);
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "{m0}"(a)
+  const uint32_t a = __builtin_amdgcn_readfirstlane(lds_address(lds));
+  uint64_t copy;
+  asm volatile("s_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+               : "=&s"(copy)
+               : "v"(off), "s"(base), "{m0}"(a)
                : "memory");
 }
 
 // The same with a full 64-bit global address per lane.
 __device__ __forceinline__ void load_to_lds16_at(const void* src, const void* lds) {
-  const uint32_t a = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(const lds_void*)lds);
+  const uint32_t a = __builtin_amdgcn_readfirstlane(lds_address(lds));
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "{m0}"(a) : "memory");
 }
 
