@@ -557,10 +557,13 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
     if ((e = hipGetLastError()) != hipSuccess) return e;
     a.beta_g = (accumulate_g || t0 > 0) ? 1.0 : 0.0;
     a.beta_e = (accumulate_e || t0 > 0) ? 1.0 : 0.0;
+    // about 32 steps per workgroup, or a whole tile where the tiles are fewer
+    // steps: splitting those as well would take the fix-up launch
     int64_t shares = (a.ntiles * a.nsteps + 31) / 32;
+    if (shares < a.ntiles && a.ntiles <= max_shares) shares = a.ntiles;
     if (shares > max_shares) shares = max_shares;
     if (shares > kGramI8MaxShares) shares = kGramI8MaxShares;
-    if (shares >= 8) shares &= ~(int64_t)7;
+    if (shares >= 8 && shares != a.ntiles) shares &= ~(int64_t)7;
     if (shares < 1) shares = 1;
     a.nshare = (int)shares;
     a.n_dp = a.ntiles / shares;

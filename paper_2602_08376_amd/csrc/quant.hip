@@ -67,11 +67,15 @@ __global__ __launch_bounds__(256) void group_row_sums_kernel(const double* __res
     const int64_t l0 = t * g, l1 = (l0 + g < m) ? l0 + g : m;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m;
          i += (int64_t)gridDim.x * 256) {
+      // (unrolled so that sixteen loads are under way; L[l][i] = 0 for l < i)
       double s = 0.0;
       if (rows) {
+#pragma unroll 16
         for (int64_t l = l0; l < l1; ++l) s += L[(int64_t)rows[l] * m + i];
       } else {
-        for (int64_t l = (l0 > i ? l0 : i); l < l1; ++l) s += L[l * m + i];   // L[l][i] = 0 for l < i
+        const int64_t d0 = i - (int64_t)threadIdx.x;   // the same for the workgroup
+#pragma unroll 16
+        for (int64_t l = l0 > d0 ? l0 : d0; l < l1; ++l) s += L[l * m + i];
       }
       Lsum[t * m + i] = s;
     }
