@@ -18,7 +18,10 @@
 // dropped ones have random signs: the largest, a2 . b4, a4 . b2 and (cross
 // term) a3 . b3, are about 2^-29 of a mean product per token.  In the Gram
 // a3 . b3 is not of random sign on the diagonal or between equal rows, where
-// leaving it out would be a bias.  The matrix cores set this kernel's time,
+// leaving it out would be a bias.  On the diagonal, where a2 . b4 and
+// a4 . b2 are the same number, the split adds it up and diagonal_kernel puts
+// it back (13 products in the diagonal tiles alone did the same but left
+// their workgroups behind: 53.2 ms instead of 50.9).  The matrix cores set this kernel's time,
 // so it goes by the number of products: seven-bit digits need thirteen for
 // three times the error (1024 rows, 32768 tokens, rms relative to
 // sqrt(G_ii G_jj): 4.8e-11; here 1.8e-11 in G, 2.6e-11 in E).  The
@@ -144,6 +147,7 @@ __device__ __forceinline__ void put4(uint32_t (&w)[kDigits][4], int at, const ui
 // lane L handles row 16 b + L % 16, tokens 16 (L / 16) .. + 15 of the step.
 // Writes the digit blocks of X~ and (with Xr) of D; zeros past m and past T.
 // With `vec` (16-byte aligned rows) a lane's 16 tokens are four 16-byte loads.
+// dg[step][row] receives the row's sum of a2 a4 over the step's tokens.
 __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq,
                                                     const float* __restrict__ Xr, int64_t m,
                                                     int64_t T, int64_t ldx, int64_t t0,
@@ -151,7 +155,8 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq
                                                     const int* __restrict__ eq,
                                                     const int* __restrict__ ed,
                                                     uint8_t* __restrict__ dq,
-                                                    uint8_t* __restrict__ dd) {
+                                                    uint8_t* __restrict__ dd,
+                                                    int* __restrict__ dg) {
   const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (wv >= nsteps * nrb) return;
@@ -206,6 +211,33 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq
     if (x)
       *reinterpret_cast<uint4*>(dd + p * plane + at) =
           make_uint4(wd[p][0], wd[p][1], wd[p][2], wd[p][3]);
+  }
+  int d24 = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w)
+    d24 = __builtin_amdgcn_sdot4((int)wq[1][w], (int)wq[3][w], d24, false);
+  d24 += __shfl_xor(d24, 16);
+  d24 += __shfl_xor(d24, 32);
+  if (lane < 16) dg[s * (nrb * 16) + b * 16 + lane] = d24;
+}
+
+// G_ii += 2 sum over the steps of dg (weight of a2 a4), 64 rows per workgroup.
+__global__ __launch_bounds__(1024) void diagonal_kernel(const int* __restrict__ dg, int64_t nsteps,
+                                                        int64_t mp, int64_t m,
+                                                        const int* __restrict__ eq,
+                                                        double* __restrict__ G) {
+  __shared__ int part[16][64];
+  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int64_t row = (int64_t)blockIdx.x * 64 + lane;   // < mp, a multiple of 128
+  int s = 0;   // |s| <= 32704 . 128 . 128 < 2^29
+#pragma unroll 4
+  for (int64_t k = grp; k < nsteps; k += 16) s += dg[k * mp + row];
+  part[grp][lane] = s;
+  __syncthreads();
+  if (grp == 0 && row < m) {
+#pragma unroll
+    for (int q = 1; q < 16; ++q) s += part[q][lane];
+    G[row * m + row] += ldexp((double)s, 2 * eq[row] + 17 - 62);
   }
 }
 
@@ -489,10 +521,11 @@ __global__ __launch_bounds__(256) void gram_i8_fixup_kernel(I8Args a) {
 // depend on the workspace a caller passes.
 int64_t gram_i8_substeps(int64_t m) {
   const int64_t mp = (m + kTile - 1) / kTile * kTile;
-  const int64_t per_token = 2 * kDigits * mp;   // split bytes per token
   int64_t budget = 64 * m * m;
   if (budget > ((int64_t)1 << 32)) budget = (int64_t)1 << 32;
-  int64_t steps = budget / per_token / kStep;
+  // whole steps of digits within the budget, then dg's share of those bytes
+  const int64_t digits = 2 * kDigits * kStep * mp;
+  int64_t steps = budget / digits * digits / (digits + (int64_t)sizeof(int) * mp);
   if (steps > 32704 / kStep) steps = 32704 / kStep;
   if (steps < 1024 / kStep) steps = 1024 / kStep;
   return steps;
@@ -507,7 +540,8 @@ size_t gram_i8_split_bytes(int64_t m) {
   const int64_t mp = (m + kTile - 1) / kTile * kTile;
   const size_t digits = (size_t)kDigits * (size_t)gram_i8_substeps(m) * (size_t)(mp / 16) *
                         kBlockBytes;
-  return 2 * digits + 2 * (size_t)mp * sizeof(int);
+  return 2 * digits + 2 * (size_t)mp * sizeof(int) +
+         (size_t)gram_i8_substeps(m) * (size_t)mp * sizeof(int);
 }
 
 hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64_t ldx,
@@ -524,6 +558,7 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
   uint8_t* dd = dq + digits;
   int* eq = reinterpret_cast<int*>(dd + digits);
   int* ed = eq + mp;
+  int* dg = ed + mp;   // [step][row]
   const int vec = (reinterpret_cast<uintptr_t>(Xq) % 16 == 0) && (ldx % 4 == 0) &&
                   (Xr == nullptr || reinterpret_cast<uintptr_t>(Xr) % 16 == 0);
   // exponents of the whole chunk (padding rows 0)
@@ -553,7 +588,7 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
     a.nsteps = (ts + kStep - 1) / kStep;
     const int64_t waves = a.nsteps * nrb;
     split_kernel<<<dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream>>>(
-        Xq, Xr, m, T, ldx, t0, a.nsteps, nrb, vec, eq, ed, dq, dd);
+        Xq, Xr, m, T, ldx, t0, a.nsteps, nrb, vec, eq, ed, dq, dd, dg);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     a.beta_g = (accumulate_g || t0 > 0) ? 1.0 : 0.0;
     a.beta_e = (accumulate_e || t0 > 0) ? 1.0 : 0.0;
@@ -576,6 +611,9 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
       gram_i8_fixup_kernel<<<dim3((unsigned)(a.nsk - 1), kFixSplit), dim3(256), 0, stream>>>(a);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
+    diagonal_kernel<<<dim3((unsigned)(mp / 64)), dim3(1024), 0, stream>>>(dg, a.nsteps, mp, m, eq,
+                                                                          G);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
 }
