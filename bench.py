@@ -37,7 +37,8 @@ METRIC = "layer quantize time (s) and columns×samples decoded/sec; % MFMA/HBM p
 PEAK_F64_MFMA_TFLOPS = 78.6     # MI355X dense fp64 matrix peak
 PEAK_I8_MFMA_TOPS = 5000.0      # MI355X dense int8 matrix peak (5.0 POP/s)
 PEAK_HBM_GBS = 8000.0
-I8_DIGIT_PRODUCTS = 13          # int8 digit products per entry and token (gram_i8.hip)
+# int8 digit products per token and entry of the Gram and of the cross term (gram_i8.hip)
+I8_GRAM_PRODUCTS, I8_CROSS_PRODUCTS = 11, 10
 
 
 def act_order_arg(args):
@@ -599,11 +600,11 @@ def main():
     # bound) W (X - X~) and its product with X~^T, 4 n m Tc
     flops = m * m * Tc + (4.0 * cfg.n * m * Tc if projected else 2.0 * m * m * Tc)
     achieved = flops / (gc_avg * 1e-3) / 1e12
-    # the int8 digit products that carry it: 13 per entry and token, over the
-    # Gram's lower triangle m (m + 1) / 2 and (unless projected) the m^2
-    # cross-term entries, 2 operations per multiply-add
-    i8_ops = (2.0 * I8_DIGIT_PRODUCTS * Tc *
-              (m * (m + 1) / 2 + (0.0 if projected else float(m) * m)))
+    # the int8 digit products that carry it, per token: over the Gram's lower
+    # triangle m (m + 1) / 2 and (unless projected) the m^2 cross-term
+    # entries, 2 operations per multiply-add
+    i8_ops = 2.0 * Tc * (I8_GRAM_PRODUCTS * m * (m + 1) / 2 +
+                         (0.0 if projected else I8_CROSS_PRODUCTS * float(m) * m))
     i8_achieved = i8_ops / (gc_avg * 1e-3) / 1e12
     paths = cfg.n * (cfg.K + 1) * len(cfg.mus)
     dec_flops = float(m) * m * paths     # m^2 per candidate path (the strict triangle, 2 FLOP/MAC)

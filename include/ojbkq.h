@@ -123,13 +123,14 @@ typedef struct {
                           solve; 0: it cannot.                             */
   int32_t gram_fp64;   /* arithmetic of the token sums X~^T X~ and
                           X~^T (X - X~) (Alg. 1 steps 2-3):
-                          0: every row split into four int8 digits of 7 bits
-                             below its power-of-two maximum (28 bits: every
-                             fp32 value within 2^-4 of the row maximum
-                             exactly), digit products summed exactly in int32
-                             on the int8 matrix cores, thirteen products per tile,
-                             combined in float64 (the Ozaki scheme); the cross
-                             term is formed from the exact fp64 difference;
+                          0: every row split into four balanced bytes below
+                             its power-of-two maximum (31 bits: every fp32
+                             value within 2^-7 of the row maximum exactly),
+                             digit products summed exactly in int32 on the
+                             int8 matrix cores, eleven of them for the Gram
+                             and ten for the cross term, combined in float64
+                             (the Ozaki scheme); the cross term is formed
+                             from the exact fp64 difference;
                           1: float64 matrix cores on the widened fp32 values
                              (exact products, float64 sums).             */
   int32_t decode_fp64; /* the decoder's lazy update of the centres by the
@@ -347,7 +348,9 @@ int ojbkq_dequant_matmul(const uint32_t* packed, const float* scales, const floa
  *   caller-owned device workspace of ojbkq_dequant_matmul_workspace_bytes(n,
  *   m) bytes (16-byte aligned; W_hat as fp16 [n, m rounded up to 64], zeros
  *   past m) and then multiplied, instead of being dequantized again for
- *   every tile of tokens: the faster form when T is large.  ENOSPACE for a
+ *   every tile of tokens: the faster form when T is large.  (For few tokens
+ *   both forms make one pass over the codes and leave the workspace as it
+ *   is.)  ENOSPACE for a
  *   smaller workspace, EINVAL for a NULL or misaligned one and for the
  *   argument errors of ojbkq_dequant_matmul.  Asynchronous on `stream`; the
  *   workspace must stay untouched until the product has run.

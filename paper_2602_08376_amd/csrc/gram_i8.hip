@@ -514,18 +514,21 @@ __global__ __launch_bounds__(256) void gram_i8_fixup_kernel(I8Args a) {
 
 }  // namespace
 
-// 64-token steps per sub-chunk: a split buffer of about 64 m^2 bytes (the
-// size of eight fp64 m x m matrices, so it stays a fixed share of the
-// workspace), at least 1024 and at most 32704 tokens (the int32 bound above),
+// 64-token steps per sub-chunk: split digits of about 64 m^2 bytes (the size
+// of eight fp64 m x m matrices, so they stay a fixed share of the workspace),
+// at least 1024 and at most 32704 tokens (the int32 bound above),
 // and at most 4 GB.  The sub-chunk length depends on m only, so results do not
 // depend on the workspace a caller passes.
 int64_t gram_i8_substeps(int64_t m) {
   const int64_t mp = (m + kTile - 1) / kTile * kTile;
   int64_t budget = 64 * m * m;
   if (budget > ((int64_t)1 << 32)) budget = (int64_t)1 << 32;
-  // whole steps of digits within the budget, then dg's share of those bytes
+  // whole steps of digits within the budget; for layers small enough for the
+  // library's static scratch dg (1/128 of that) takes its share of the same
+  // bytes, beyond them it comes on top
   const int64_t digits = 2 * kDigits * kStep * mp;
-  int64_t steps = budget / digits * digits / (digits + (int64_t)sizeof(int) * mp);
+  int64_t steps = budget / digits;
+  if (m <= 2048) steps = steps * digits / (digits + (int64_t)sizeof(int) * mp);
   if (steps > 32704 / kStep) steps = 32704 / kStep;
   if (steps < 1024 / kStep) steps = 1024 / kStep;
   return steps;

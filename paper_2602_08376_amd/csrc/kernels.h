@@ -63,7 +63,7 @@ hipError_t gram_cross(const float* Xq, const float* Xr, int64_t m, int64_t T, in
                       const uint32_t* tile_list, void* scratch, int max_shares,
                       hipStream_t stream);
 // The same sums on the int8 matrix cores (gram_i8.hip): every row of X_q
-// and of D = X_ref - X_q split into four int8 digits below its power-of-two
+// and of D = X_ref - X_q split into four balanced bytes below its power-of-two
 // maximum, digit products summed exactly in int32, combined in fp64.
 //   G (lower triangle by 128-tiles) = [G +] X_q X_q^T
 //   E (all of it, only if Xr != nullptr) = [E +] X_q (X_ref - X_q)^T
