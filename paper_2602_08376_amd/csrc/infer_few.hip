@@ -74,6 +74,12 @@ __global__ __launch_bounds__(512) void dequant_few_kernel(DqArgs a) {
   constexpr int kRed = RB * NB * 256;   // floats of a wave's sums
   constexpr int kLds = 8 * (kWaveX * 2 > kRed * 4 ? kWaveX * 2 : kRed * 4);
   __shared__ __align__(16) uint8_t lds[kLds];
+  // A loop without masks for whole chunks, and loads without per-row checks,
+  // where the registers hold a second copy of the code (us for n x 4096 x T
+  // with / without the first: 14336 x 24, RB = NB = 2: 24.7 / 26.7; 4096 x
+  // 512, RB = NB = 4, both: 300 / 71, with hundreds of registers spilled).
+  constexpr bool kTwice = RB <= 2 && RB * NB <= 4;
+  constexpr bool kQuick = RB * NB < 16;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, g4 = lane >> 4;
@@ -130,7 +136,7 @@ __global__ __launch_bounds__(512) void dequant_few_kernel(DqArgs a) {
         st.z[x][1] = zrow[x][g1];
       }
     }
-    if (by_piece && !a.perm && k0 + kChunk < a.m) {
+    if (kQuick && by_piece && !a.perm && k0 + kChunk < a.m) {
       // (whole, and without X's last row)
       const uint16_t* src = a.X + (k0 + prow0) * a.ldx + (tp < a.T ? tp : 0);
 #pragma unroll
@@ -193,8 +199,7 @@ __global__ __launch_bounds__(512) void dequant_few_kernel(DqArgs a) {
   for (int x = 0; x < RB; ++x)
 #pragma unroll
     for (int y = 0; y < NB; ++y) acc[x][y] = f4{0.f, 0.f, 0.f, 0.f};
-  auto products = [&](int64_t c, const Stage& st, auto all) {
-    constexpr bool whole = decltype(all)::value;
+  auto products = [&](int64_t c, const Stage& st, auto whole) {
     // codes of this lane that exist (all but in a last ragged chunk; one past
     // the end need not give a finite weight)
     const int64_t left = a.m - (c * kChunk + 32 * g4);
@@ -243,7 +248,10 @@ __global__ __launch_bounds__(512) void dequant_few_kernel(DqArgs a) {
       put(st);
       const Stage cur = st;
       if (c + 8 < nch) fetch(c + 8, st);
-      if ((c + 1) * kChunk <= a.m)
+      const bool whole = (c + 1) * kChunk <= a.m;
+      if constexpr (!kTwice)
+        products(c, cur, whole);
+      else if (whole)
         products(c, cur, std::true_type{});
       else
         products(c, cur, std::false_type{});
