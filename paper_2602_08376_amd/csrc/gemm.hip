@@ -363,9 +363,8 @@ hipError_t launch_tile(GemmArgs g, hipStream_t s) {
 // dealt to 256 of them, times what a block costs in that tile (the small
 // tiles read their operands more often): 1, 1.15 and 1.6.  A product of few
 // 128-wide tiles leaves most CUs idle and runs at one tile's latency: 64 x 128
-// x 128 took 25 us and takes 6 with 32-wide tiles, a leaf of the triangular
-// solve (1000 x 128 x 128) 43 and 12, 1000 x 2500 x 2500 with 64-wide ones 410
-// and 350.  The lower-triangle form keeps 128: its callers count on whole
+// x 128 took 25 us and takes 6 with 32-wide tiles, 1000 x 2500 x 2500 with
+// 64-wide ones 410 and 350.  The lower-triangle form keeps 128: its callers count on whole
 // 128-wide tiles.
 template <typename TA, typename TB, bool AK, bool BK, bool BDIFF>
 hipError_t launch(const GemmArgs& g, hipStream_t s) {
@@ -375,8 +374,12 @@ hipError_t launch(const GemmArgs& g, hipStream_t s) {
       return (tiles + 255) / 256 * (t / 32) * (t / 32) * per_block;
     };
     const int64_t c128 = cost(128, 100), c64 = cost(64, 115), c32 = cost(32, 160);
-    if (!g.lower && c32 < c64 && c32 < c128) return launch_tile<TA, TB, AK, BK, BDIFF, 32>(g, s);
-    if (!g.lower && c64 < c128) return launch_tile<TA, TB, AK, BK, BDIFF, 64>(g, s);
+    // in place (C is A: the leaves of the triangular solve, the factor's
+    // panels) one tile must hold whole rows of C, or a workgroup would read
+    // columns that another one has already written
+    const int64_t least = g.lower ? 128 : (static_cast<const void*>(g.C) == g.A ? g.N : 0);
+    if (least <= 32 && c32 < c64 && c32 < c128) return launch_tile<TA, TB, AK, BK, BDIFF, 32>(g, s);
+    if (least <= 64 && c64 < c128) return launch_tile<TA, TB, AK, BK, BDIFF, 64>(g, s);
   }
   return launch_tile<TA, TB, AK, BK, BDIFF, 128>(g, s);
 }

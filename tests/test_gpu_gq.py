@@ -57,3 +57,21 @@ def test_decoder_input(m, n, mu):
         # token, of random sign) through a well-conditioned factor
         bound = bound + 1e-8 * np.abs(U).max()
     assert np.all(np.abs(gq - want) <= bound + 1e-300)
+
+
+def test_products_in_place_give_the_same_every_time():
+    # the triangular solve's leaves overwrite their own left operand: with
+    # tiles narrower than a leaf, workgroups would read each other's results
+    m, n = 6400, 128
+    g = torch.Generator(device=DEV).manual_seed(9)
+    X = torch.randn(m, 4096, generator=g, device=DEV)
+    Xq = X + 0.05 * torch.randn(m, 4096, generator=g, device=DEV)
+    W = torch.randn(n, m, generator=g, device=DEV) * 0.02
+    s = ok.LayerSolver(m, n, 4, 64, 0, 1)
+    s.accumulate(X, Xq)
+    s.solve(W, 0.5)
+    first = s.inspect("gq")
+    for _ in range(40):
+        s.solve(W, 0.5)
+        assert torch.equal(s.inspect("gq"), first)
+    s.close()
