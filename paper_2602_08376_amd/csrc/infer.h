@@ -4,6 +4,7 @@
 
 #include "device.h"
 #include "kernels.h"
+#include "x_piece.h"
 
 namespace ojbkq {
 

@@ -370,7 +370,7 @@ __global__ __launch_bounds__(2 * kTile, kTile == 256 ? 1 : 2) void dequant_matmu
   // array: an array captured by these lambdas is moved to LDS) while the
   // products run, then stored.  Features past the last one are zero.  Eight
   // tokens that reach past the last one are read on into the next row (they
-  // feed only outputs never stored), in X's last row one by one.
+  // feed only outputs never stored), where that is not inside X one by one.
   const int bc = tid % kSlots, br = tid / kSlots;
   typedef uint32_t Runs __attribute__((ext_vector_type(16)));
   typedef uint32_t Any4 __attribute__((ext_vector_type(4), aligned(2)));
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(2 * kTile, kTile == 256 ? 1 : 2) void dequant_matmu
       Any4 v = Any4{0u, 0u, 0u, 0u};
       if (k0 + br + 16 * q < a.m && xt < a.T) {
         const uint16_t* src = a.X + xr[q] * a.ldx + xt;
-        if (xt + 8 <= a.T || xr[q] + 1 < a.m) {
+        if (x_piece_inside(xr[q], xt, a.m, a.T)) {
           v = *reinterpret_cast<const Any4*>(src);
         } else {
 #pragma unroll

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(512) void dequant_few_kernel(DqArgs a) {
         if (k < a.m && tp < a.T) {
           const int64_t r = x_row(a, k);
           const uint16_t* src = a.X + r * a.ldx + tp;
-          if (tp + 8 <= a.T || r + 1 < a.m) {
+          if (x_piece_inside(r, tp, a.m, a.T)) {
             v = *reinterpret_cast<const Any4*>(src);
           } else {
 #pragma unroll

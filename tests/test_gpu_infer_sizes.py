@@ -52,6 +52,12 @@ def test_pack_codes(bits, n, m, permuted):
     (2100, 192, 1000, 1, 64, 8, False),
     (4300, 200, 4100, 4, 64, 0, False),  # the large tiles, ragged in every direction
     (4300, 200, 4101, 3, 64, 2, True),
+    (32769, 72, 1, 4, 0, 0, False),      # an output head: the last rows of X hold fewer than
+    (32769, 130, 2, 3, 64, 0, True),     # eight elements from their first on
+    (33000, 65, 3, 4, 16, 0, False),
+    (32769, 72, 7, 5, 0, 1, False),
+    (32769, 72, 9, 2, 0, 0, False),
+    (32769, 130, 65, 4, 64, 0, True),
 ])
 def test_product_at_the_edges_of_its_kernels(n, m, T, bits, group, ld, permuted):
     rng = np.random.default_rng(n + m + T)
