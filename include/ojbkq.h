@@ -127,10 +127,11 @@ typedef struct {
                              its power-of-two maximum (31 bits: every fp32
                              value within 2^-7 of the row maximum exactly),
                              digit products summed exactly in int32 on the
-                             int8 matrix cores, eleven of them for the Gram
-                             and ten for the cross term, combined in float64
-                             (the Ozaki scheme); the cross term is formed
-                             from the exact fp64 difference;
+                             int8 matrix cores, thirteen of the sixteen (the
+                             others are at most 2^-38.9 of the two maxima's
+                             product per token), combined in float64 (the
+                             Ozaki scheme); the cross term is formed from the
+                             exact fp64 difference;
                           1: float64 matrix cores on the widened fp32 values
                              (exact products, float64 sums).             */
   int32_t decode_fp64; /* the decoder's lazy update of the centres by the

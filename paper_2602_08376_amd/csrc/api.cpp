@@ -138,7 +138,7 @@ inline bool route_q(const Shape& s) { return 2 * s.n > s.m; }
 // term's 2 m^2 (and no W E^T at solve time).  Against the fp64 mixed product
 // that pays once n is below about 0.4 m (the general GEMM reaches about 0.75
 // of the MFMA peak, the Gram kernel about 0.89); against the int8 cross term
-// (ten digit products per entry at about 60 times the fp64 rate) only once n
+// (thirteen digit products per entry at about 60 times the fp64 rate) only once n
 // is below about m / 10.
 inline bool route_p(const Shape& s) {
   return s.gram_i8 ? 10 * s.n <= s.m : 5 * s.n <= 2 * s.m;

@@ -13,20 +13,24 @@
 // of two rows is then
 //   2^(e_i + e_j - 14) sum_w 2^(-8 (w - 2)) sum_{p+q=w} a_p . b_q,
 // whose inner sums are int8 dot products accumulated exactly in int32 by
-// v_mfma_i32_16x16x64_i8, one int32 accumulator per w.  The ten digit
-// products with p + q <= 5 are kept, and for the Gram a3 . b3 too.  The
-// dropped ones have random signs: the largest, a2 . b4, a4 . b2 and (cross
-// term) a3 . b3, are about 2^-29 of a mean product per token.  In the Gram
-// a3 . b3 is not of random sign on the diagonal or between equal rows, where
-// leaving it out would be a bias.  On the diagonal, where a2 . b4 and
-// a4 . b2 are the same number, the split adds it up and diagonal_kernel puts
-// it back (13 products in the diagonal tiles alone did the same but left
-// their workgroups behind: 53.2 ms instead of 50.9).  The matrix cores set this kernel's time,
-// so it goes by the number of products: seven-bit digits need thirteen for
-// three times the error (1024 rows, 32768 tokens, rms relative to
-// sqrt(G_ii G_jj): 4.8e-11; here 1.8e-11 in G, 2.6e-11 in E).  The
-// accumulators are flushed to fp64 once per sub-chunk of at most 32704 tokens
-// (|sum| <= 4 . 128 . 128 . 32704 < 2^31).
+// v_mfma_i32_16x16x64_i8, one int32 accumulator per w.  The thirteen digit
+// products with p + q <= 6 are kept, in both sums; the dropped ones are at most
+// 2^-38.9 of 2^(e_i + e_j) at every token, whatever their signs.
+// That matters: between constant or parallel rows, and in E where D follows
+// X~, the digits at a token go together and a dropped product is a bias.  Ten
+// products (p + q <= 5) with what was missing on the Gram's diagonal put back
+// took 51.3 ms at 4096 rows x 262144 tokens instead of 58.5, but on such rows
+// they are 20 to 500 times less exact than thirteen products of seven-bit
+// digits (28 bits), which took 63.  Largest error relative to the root of the
+// two rows' norms, 24 rows x 32768 tokens, seven-bit / ten / thirteen:
+//   independent Gaussian rows           2.5e-10 / 8.6e-11 / 3.3e-12
+//   E where X = -X~                     2.0e-10 / 5.1e-9  / 3.4e-12
+//   E where X = 1.25 X~, parallel rows  4.4e-12 / 2.2e-9  / 3.6e-14
+//   constant rows                       9.3e-11 / 1.2e-9  / 5.2e-12
+//   rows in fp16                        4.6e-12 / 1.7e-11 / 1.1e-14
+// The accumulators are flushed to fp64 once per sub-chunk of at most 32768
+// tokens: |a1| <= 127 (digit_exponent), so the largest of them, w = 5, stays
+// below (2 . 127 . 128 + 2 . 128 . 128) . 32768 < 2^31.
 //
 // Layout of the split operands (written by split_kernel): per tensor, digit
 // plane p, 64-token step s and 16-row block b one 1 KB block in the order the
@@ -147,7 +151,6 @@ __device__ __forceinline__ void put4(uint32_t (&w)[kDigits][4], int at, const ui
 // lane L handles row 16 b + L % 16, tokens 16 (L / 16) .. + 15 of the step.
 // Writes the digit blocks of X~ and (with Xr) of D; zeros past m and past T.
 // With `vec` (16-byte aligned rows) a lane's 16 tokens are four 16-byte loads.
-// dg[step][row] receives the row's sum of a2 a4 over the step's tokens.
 __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq,
                                                     const float* __restrict__ Xr, int64_t m,
                                                     int64_t T, int64_t ldx, int64_t t0,
@@ -155,8 +158,7 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq
                                                     const int* __restrict__ eq,
                                                     const int* __restrict__ ed,
                                                     uint8_t* __restrict__ dq,
-                                                    uint8_t* __restrict__ dd,
-                                                    int* __restrict__ dg) {
+                                                    uint8_t* __restrict__ dd) {
   const int64_t wv = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (wv >= nsteps * nrb) return;
@@ -212,33 +214,6 @@ __global__ __launch_bounds__(256) void split_kernel(const float* __restrict__ Xq
       *reinterpret_cast<uint4*>(dd + p * plane + at) =
           make_uint4(wd[p][0], wd[p][1], wd[p][2], wd[p][3]);
   }
-  int d24 = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w)
-    d24 = __builtin_amdgcn_sdot4((int)wq[1][w], (int)wq[3][w], d24, false);
-  d24 += __shfl_xor(d24, 16);
-  d24 += __shfl_xor(d24, 32);
-  if (lane < 16) dg[s * (nrb * 16) + b * 16 + lane] = d24;
-}
-
-// G_ii += 2 sum over the steps of dg (weight of a2 a4), 64 rows per workgroup.
-__global__ __launch_bounds__(1024) void diagonal_kernel(const int* __restrict__ dg, int64_t nsteps,
-                                                        int64_t mp, int64_t m,
-                                                        const int* __restrict__ eq,
-                                                        double* __restrict__ G) {
-  __shared__ int part[16][64];
-  const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-  const int64_t row = (int64_t)blockIdx.x * 64 + lane;   // < mp, a multiple of 128
-  int s = 0;   // |s| <= 32704 . 128 . 128 < 2^29
-#pragma unroll 4
-  for (int64_t k = grp; k < nsteps; k += 16) s += dg[k * mp + row];
-  part[grp][lane] = s;
-  __syncthreads();
-  if (grp == 0 && row < m) {
-#pragma unroll
-    for (int q = 1; q < 16; ++q) s += part[q][lane];
-    G[row * m + row] += ldexp((double)s, 2 * eq[row] + 17 - 62);
-  }
 }
 
 // ---- contraction ----------------------------------------------------------------
@@ -272,19 +247,18 @@ __device__ __forceinline__ v4i mfma_i8(v4i a, v4i b, v4i c) {
 // Steps [c0, c1) of one tile; a whole tile goes to G / E, a part to slot
 // `slot` of share r.  Two LDS stages of one step each.
 constexpr int kFirst = 5, kSecond = 3;   // loads per wave and step of the two digit groups
-template <bool kCross>
 __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_t c0, int64_t c1,
                                            int64_t r, int& slot, uint8_t* sbuf) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;   // 32x64 block of the tile
   const uint32_t te = a.tile_list[tile];
+  const bool cross = (te >> 31) != 0;
   const int64_t ti = (te >> 16) & 0x7fff, tj = te & 0xffff;
-  const int* eB = kCross ? a.ed : a.eq;
+  const int* eB = cross ? a.ed : a.eq;
 
-  constexpr int kW = kCross ? 4 : 5;
-  v4i acc[kW][2][4];   // [w - 2][row block][col block]
+  v4i acc[5][2][4];   // [w - 2][row block][col block]
 #pragma unroll
-  for (int c = 0; c < kW; ++c)
+  for (int c = 0; c < 5; ++c)
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -295,7 +269,7 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
   // digits 1..3 of A and 3, 4 of B, and three of the second, the others
   // 32-bit offsets into the split buffer (at most 4 GB: gram_i8_substeps)
   const uint32_t plane = (uint32_t)a.nsteps * (uint32_t)a.nrb * kBlockBytes;
-  const uint32_t b_at = kCross ? (uint32_t)(a.dd - a.dq) : 0u;
+  const uint32_t b_at = cross ? (uint32_t)(a.dd - a.dq) : 0u;
   uint32_t src[8];
   int dst[8];
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
@@ -320,19 +294,17 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
   // One step is a chain of digit products (p, q), eight MFMAs each, ordered so
   // that every fragment is read one or two products ahead of its use, and the
   // step's stage falls into two groups of digits: the first is read by the
-  // middle of the step, the second from there to three products before the
+  // middle of the step, the second from there to four products before the
   // end.  At each of these two points stands a barrier, after which the
   // group's buffer takes the same group of step c + 2, one load at a time
   // between the products (issued together they hold up the products behind
   // them), and the group read next has landed: its loads are a step and a
   // half old, older than the wave's last eight.  The first fragments of the
   // next step are read beside the last products, so no wave waits at a step's
-  // start.  4096 rows x 262144 tokens, both sums: 49 ms; 63 ms with thirteen
-  // products, every wave reading its first fragments behind one barrier per
-  // step and a step's loads issued together (with eleven products that took
-  // 57 ms, one barrier three products before the end and the loads together
-  // behind it 51 ms).  Without any loads it is 42 ms, with neither loads nor
-  // fragment reads 39 ms: the matrix cores alone, at the clock they hold.
+  // start.  The barriers stand a product after the last reads they wait for.
+  // 4096 rows x 262144 tokens, both sums: 58.5 ms (with the barriers right
+  // behind those reads 60.7; with one barrier per step, a step's loads issued
+  // together behind it and its first fragments read there 63).
   v4i fa[kDigits][2], fb[2][4];
   auto read_a = [&](const uint8_t* st, int p) {
 #pragma unroll
@@ -347,11 +319,11 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
   };
   auto products = [&](int p, int q) {
     __builtin_amdgcn_sched_barrier(0);   // the reads before go out first
-    const int w = p == 2 && q == 2 ? kW - 1 : p + q;
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
-      for (int y = 0; y < 4; ++y) acc[w][x][y] = mfma_i8(fa[p][x], fb[q & 1][y], acc[w][x][y]);
+      for (int y = 0; y < 4; ++y) 
+        acc[p + q][x][y] = mfma_i8(fa[p][x], fb[q & 1][y], acc[p + q][x][y]);
     __builtin_amdgcn_sched_barrier(0);
   };
   auto meet = [&] {
@@ -368,18 +340,19 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
   for (int64_t c = c0; c < c1; ++c) {
     const uint8_t* cur = sbuf + ((c - c0) & 1) * kStageBytes;
     const uint8_t* nxt = sbuf + ((c + 1 - c0) & 1) * kStageBytes;
-    read_b(cur, 2);
-    products(0, 3);
     read_a(cur, 1);
-    products(0, 2);
+    products(0, 3);
+    read_b(cur, 2);
+    products(1, 3);
     read_a(cur, 2);
-    products(1, 2);
+    products(0, 2);
     meet();   // the first group is read, the second in LDS
-    read_b(cur, 1);
+    products(1, 2);
     load(c + 2, 0);
-    if constexpr (!kCross) products(2, 2);
-    read_a(cur, 3);
+    read_b(cur, 1);
+    products(2, 2);
     load(c + 2, 1);
+    read_a(cur, 3);
     products(0, 1);
     load(c + 2, 2);
     products(1, 1);
@@ -387,11 +360,12 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
     load(c + 2, 3);
     products(2, 1);
     load(c + 2, 4);
-    products(0, 0);
+    products(3, 1);
     meet();   // the second group is read, the next step's first in LDS
+    products(0, 0);
     load(c + 2, 5);
     products(1, 0);
-    read_a(nxt, 0);    // (past the last step nothing uses them)
+    read_a(nxt, 0);   // (past the last step nothing uses them)
     load(c + 2, 6);
     products(2, 0);
     read_b(nxt, 3);
@@ -401,8 +375,8 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
   wait_loads();   // none may land in the next segment's stages
 
   const bool whole = (c0 == 0 && c1 == a.nsteps);
-  double* C = kCross ? a.E : a.G;
-  const double beta = kCross ? a.beta_e : a.beta_g;
+  double* C = cross ? a.E : a.G;
+  const double beta = cross ? a.beta_e : a.beta_g;
   double* P = a.part + (r * 2 + slot) * kSlotElems;
   const int64_t I0 = ti * kTile, J0 = tj * kTile;
 #pragma unroll
@@ -415,7 +389,7 @@ __device__ __forceinline__ void i8_segment(const I8Args& a, int64_t tile, int64_
       for (int v = 0; v < 4; ++v) {
         const int li = wr * 32 + x * 16 + 4 * (lane >> 4) + v;
         // sum over w, smallest weight first, then the rows' power-of-two scale
-        double s = kCross ? 0.0 : (double)acc[kW - 1][x][y][v] * 0x1p-32;
+        double s = (double)acc[4][x][y][v] * 0x1p-32;
         s += (double)acc[3][x][y][v] * 0x1p-24;
         s += (double)acc[2][x][y][v] * 0x1p-16;
         s += (double)acc[1][x][y][v] * 0x1p-8;
@@ -459,10 +433,7 @@ __global__ __launch_bounds__(kThreads, 1) void gram_i8_kernel(I8Args a) {
     } else {
       break;
     }
-    if ((a.tile_list[tile] >> 31) != 0)
-      i8_segment<true>(a, tile, c0, c1, r, slot, sbuf);
-    else
-      i8_segment<false>(a, tile, c0, c1, r, slot, sbuf);
+    i8_segment(a, tile, c0, c1, r, slot, sbuf);
   }
 }
 
@@ -514,22 +485,21 @@ __global__ __launch_bounds__(256) void gram_i8_fixup_kernel(I8Args a) {
 
 }  // namespace
 
-// 64-token steps per sub-chunk: split digits of about 64 m^2 bytes (the size
-// of eight fp64 m x m matrices, so they stay a fixed share of the workspace),
-// at least 1024 and at most 32704 tokens (the int32 bound above),
-// and at most 4 GB.  The sub-chunk length depends on m only, so results do not
-// depend on the workspace a caller passes.
+// 64-token steps per sub-chunk: a split buffer of about 64 m^2 bytes (the
+// size of eight fp64 m x m matrices, so it stays a fixed share of the
+// workspace), at least 1024 and at most 32768 tokens (the int32 bound above),
+// and at most 4 GB; one step in 128 less for layers that the library's static
+// scratch may have to hold, which leaves those at its edge the room they have
+// had.  The sub-chunk length depends on m only, so results do not depend on
+// the workspace a caller passes.
 int64_t gram_i8_substeps(int64_t m) {
   const int64_t mp = (m + kTile - 1) / kTile * kTile;
+  const int64_t per_token = 2 * kDigits * mp;   // split bytes per token
   int64_t budget = 64 * m * m;
   if (budget > ((int64_t)1 << 32)) budget = (int64_t)1 << 32;
-  // whole steps of digits within the budget; for layers small enough for the
-  // library's static scratch dg (1/128 of that) takes its share of the same
-  // bytes, beyond them it comes on top
-  const int64_t digits = 2 * kDigits * kStep * mp;
-  int64_t steps = budget / digits;
-  if (m <= 2048) steps = steps * digits / (digits + (int64_t)sizeof(int) * mp);
-  if (steps > 32704 / kStep) steps = 32704 / kStep;
+  int64_t steps = budget / per_token / kStep;
+  if (m <= 2048) steps -= (steps + 127) / 128;
+  if (steps > 32768 / kStep) steps = 32768 / kStep;
   if (steps < 1024 / kStep) steps = 1024 / kStep;
   return steps;
 }
@@ -543,8 +513,7 @@ size_t gram_i8_split_bytes(int64_t m) {
   const int64_t mp = (m + kTile - 1) / kTile * kTile;
   const size_t digits = (size_t)kDigits * (size_t)gram_i8_substeps(m) * (size_t)(mp / 16) *
                         kBlockBytes;
-  return 2 * digits + 2 * (size_t)mp * sizeof(int) +
-         (size_t)gram_i8_substeps(m) * (size_t)mp * sizeof(int);
+  return 2 * digits + 2 * (size_t)mp * sizeof(int);
 }
 
 hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64_t ldx,
@@ -561,7 +530,6 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
   uint8_t* dd = dq + digits;
   int* eq = reinterpret_cast<int*>(dd + digits);
   int* ed = eq + mp;
-  int* dg = ed + mp;   // [step][row]
   const int vec = (reinterpret_cast<uintptr_t>(Xq) % 16 == 0) && (ldx % 4 == 0) &&
                   (Xr == nullptr || reinterpret_cast<uintptr_t>(Xr) % 16 == 0);
   // exponents of the whole chunk (padding rows 0)
@@ -591,7 +559,7 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
     a.nsteps = (ts + kStep - 1) / kStep;
     const int64_t waves = a.nsteps * nrb;
     split_kernel<<<dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, stream>>>(
-        Xq, Xr, m, T, ldx, t0, a.nsteps, nrb, vec, eq, ed, dq, dd, dg);
+        Xq, Xr, m, T, ldx, t0, a.nsteps, nrb, vec, eq, ed, dq, dd);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     a.beta_g = (accumulate_g || t0 > 0) ? 1.0 : 0.0;
     a.beta_e = (accumulate_e || t0 > 0) ? 1.0 : 0.0;
@@ -614,9 +582,6 @@ hipError_t gram_i8(const float* Xq, const float* Xr, int64_t m, int64_t T, int64
       gram_i8_fixup_kernel<<<dim3((unsigned)(a.nsk - 1), kFixSplit), dim3(256), 0, stream>>>(a);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    diagonal_kernel<<<dim3((unsigned)(mp / 64)), dim3(1024), 0, stream>>>(dg, a.nsteps, mp, m, eq,
-                                                                          G);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
 }

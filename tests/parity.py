@@ -38,11 +38,11 @@ U_BAND = 1e-6
 # follows from them to first order (lambda^2, the factor, matrix-free probes,
 # the Gram diagonal that orders act-order features), by the arithmetic of the
 # Gram stage (ojbkq_params.gram_fp64):
-#   int8: every value is kept to 28 bits below its row's power-of-two maximum
-#     2^e (error <= 2^(e-28)), so a product x_i x_j loses at most about
-#     2^-27 2^(e_i + e_j) per token, with random signs over the tokens: about
-#     sqrt(T) 2^-27 2^(e_i + e_j) in all, measured 1e-10 to 5e-10 of
-#     sqrt(G_ii G_jj) on these workloads; 1e-8 leaves a 20x margin;
+#   int8: every value is kept to 31 bits below its row's power-of-two maximum
+#     2^e (error <= 2^(e-32)), so a product x_i x_j loses at most 2^-30.9
+#     2^(e_i + e_j) per token (test_gpu_gram.py holds the sums to that), with
+#     random signs over the tokens: about 3e-12 of sqrt(G_ii G_jj) between
+#     Gaussian rows of 32768 tokens.  1e-8 is far above that;
 #   fp64: exact products, float64 sums.
 GRAM_RTOL = {"int8": 1e-8, "fp64": 1e-11}
 # the same for quantities that go through a solve with H (Rbar qbar, whose

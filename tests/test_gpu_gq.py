@@ -53,7 +53,7 @@ def test_decoder_input(m, n, mu):
         E = Q @ (X.numpy().astype(np.float64) - Q).T
         U = (1 - mu) * np.linalg.solve(L, E @ Wn.T).T
         want = want + U
-        # the sums' own error (below 2^-29 of the row maxima's products a
+        # the sums' own error (below 2^-30 of the row maxima's products a
         # token, of random sign) through a well-conditioned factor
         bound = bound + 1e-8 * np.abs(U).max()
     assert np.all(np.abs(gq - want) <= bound + 1e-300)
