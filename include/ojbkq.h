@@ -349,9 +349,9 @@ int ojbkq_dequant_matmul(const uint32_t* packed, const float* scales, const floa
  *   caller-owned device workspace of ojbkq_dequant_matmul_workspace_bytes(n,
  *   m) bytes (16-byte aligned; W_hat as fp16 [n, m rounded up to 64], zeros
  *   past m) and then multiplied, instead of being dequantized again for
- *   every tile of tokens: the faster form when T is large.  (For few tokens
- *   both forms make one pass over the codes and leave the workspace as it
- *   is.)  ENOSPACE for a
+ *   every tile of tokens: the faster form when T is large.  (For few tokens,
+ *   T <= 32 with m >= 512, and for products small enough, both forms make one
+ *   pass over the codes and leave the workspace as it is.)  ENOSPACE for a
  *   smaller workspace, EINVAL for a NULL or misaligned one and for the
  *   argument errors of ojbkq_dequant_matmul.  Asynchronous on `stream`; the
  *   workspace must stay untouched until the product has run.

@@ -874,8 +874,13 @@ hipError_t launch_dequant_matmul(const uint32_t* P, const float* S, const float*
   // tokens per CU.  One pass over the codes, the workspace not needed.  (us at
   // m = 4096, 4 bits, against the 128-wide tiles below with W_hat once: n =
   // 4096, T = 512: 69 / 75, T = 1000: 137 / 77; n = 14336, T = 128: 69 / 84,
-  // T = 256: 133 / 87.)
-  if ((n + 63) / 64 * ((T + 63) / 64) <= 512) return launch_dequant_few(a, bits, stream);
+  // T = 256: 133 / 87.)  Up to 32 tokens that holds for any number of channels
+  // (an output head), where forming W_hat costs several passes over the codes,
+  // unless the rows are short: n = 128256, T = 1: 192 / 657, T = 32: 192 / 617;
+  // n = 131072, m = 512, T = 16: 56 / 66, with 8 bits 71 / 70; m = 256: 52 / 45.
+  // (Codes of several layers in turn, so that they come from memory.)
+  if ((n + 63) / 64 * ((T + 63) / 64) <= 512 || (T <= 32 && m >= 512))
+    return launch_dequant_few(a, bits, stream);
   if (workspace) {
     // W_hat once, then the product reads it instead of dequantizing every tile
     _Float16* W = static_cast<_Float16*>(workspace);

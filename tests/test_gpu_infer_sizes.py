@@ -58,6 +58,10 @@ def test_pack_codes(bits, n, m, permuted):
     (32769, 72, 7, 5, 0, 1, False),
     (32769, 72, 9, 2, 0, 0, False),
     (32769, 130, 65, 4, 64, 0, True),
+    (32769, 511, 32, 4, 0, 0, False),    # either side of the few-token product's limits
+    (32769, 512, 32, 3, 64, 0, True),
+    (32769, 512, 33, 4, 64, 0, False),
+    (33000, 520, 1, 8, 16, 0, False),
 ])
 def test_product_at_the_edges_of_its_kernels(n, m, T, bits, group, ld, permuted):
     rng = np.random.default_rng(n + m + T)
@@ -76,6 +80,7 @@ def test_product_at_the_edges_of_its_kernels(n, m, T, bits, group, ld, permuted)
     # with a permutation the scales are those of the permuted groups
     args = (P, torch.from_numpy(S).to(DEV), torch.from_numpy(Z).to(DEV), m, bits, group, X)
     Y = ok.dequant_matmul(*args, perm=dperm, workspace=True)
+    # (where both make one pass over the codes, the same kernel twice)
     assert torch.equal(Y, ok.dequant_matmul(*args, perm=dperm, workspace=False))
     W16 = oi.dequantize_fp16(codes if perm is None else codes[:, perm], S, Z, group)
     xp = x16 if perm is None else x16[perm]
@@ -88,3 +93,20 @@ def test_product_at_the_edges_of_its_kernels(n, m, T, bits, group, ld, permuted)
     # every other element against float64 on the GPU
     full = torch.from_numpy(W16).to(DEV).double() @ torch.from_numpy(xp).to(DEV).double()
     assert float((Y.double() - full).norm() / full.norm()) < 1e-6
+
+
+@pytest.mark.parametrize("n,m,T,one_pass", [(32769, 512, 1, True), (32769, 512, 32, True),
+                                            (32769, 512, 33, False), (32769, 504, 32, False),
+                                            (4096, 512, 100, True)])
+def test_few_tokens_leave_the_workspace(n, m, T, one_pass):
+    g = torch.Generator(device=DEV).manual_seed(n + T)
+    P = torch.randint(0, 2 ** 31 - 1, (n, ok.packed_words(m, 4)), generator=g, device=DEV,
+                      dtype=torch.int32)
+    S = torch.rand(n, 1, generator=g, device=DEV) + 0.5
+    Z = torch.full((n, 1), 8.0, device=DEV)
+    X = torch.randn(m, T, generator=g, device=DEV).half()
+    ws = torch.full((int(ok.library().ojbkq_dequant_matmul_workspace_bytes(n, m)),), 0xAB,
+                    dtype=torch.uint8, device=DEV)
+    Y = ok.dequant_matmul(P, S, Z, m, 4, 0, X, workspace=ws)
+    assert bool((ws == 0xAB).all()) == one_pass
+    assert torch.equal(Y, ok.dequant_matmul(P, S, Z, m, 4, 0, X))
