@@ -491,8 +491,9 @@ def dequant_matmul(packed: torch.Tensor, scales: torch.Tensor, zeros: torch.Tens
     contiguous) and W_hat from the packed codes (packed with ``perm`` when one
     is given).  ``workspace``: True (a device buffer of
     ``ojbkq_dequant_matmul_workspace_bytes`` is allocated here and W_hat formed
-    there once, ``ojbkq_dequant_matmul_ws``), a uint8 device tensor to use as
-    that buffer, or False (``ojbkq_dequant_matmul``: dequantized per tile, no
+    there once, ``ojbkq_dequant_matmul_ws``; no buffer for the few tokens, T <=
+    32 with m >= 512, that never use it), a uint8 device tensor to use as that
+    buffer, or False (``ojbkq_dequant_matmul``: dequantized per tile, no
     buffer)."""
     dev = packed.device
     _need(packed, "packed", torch.int32, device=dev)
@@ -508,7 +509,7 @@ def dequant_matmul(packed: torch.Tensor, scales: torch.Tensor, zeros: torch.Tens
     T, ld = _rows_view(X, "X", m)
     perm = _perm_arg(perm, m, dev)
     Y = torch.empty(n, T, dtype=torch.float32, device=dev)
-    if workspace is False:
+    if workspace is False or (workspace is True and T <= 32 and m >= 512):
         _check(library().ojbkq_dequant_matmul(_ptr(packed), _ptr(scales), _ptr(zeros), n, m,
                                               int(bits), int(group), _ptr(X), T, ld, _ptr(perm),
                                               _ptr(Y), T, _stream(dev)))

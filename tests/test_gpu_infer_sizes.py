@@ -110,3 +110,20 @@ def test_few_tokens_leave_the_workspace(n, m, T, one_pass):
     Y = ok.dequant_matmul(P, S, Z, m, 4, 0, X, workspace=ws)
     assert bool((ws == 0xAB).all()) == one_pass
     assert torch.equal(Y, ok.dequant_matmul(P, S, Z, m, 4, 0, X))
+
+
+def test_few_tokens_allocate_no_workspace():
+    # by default the binding allocates the workspace, but not for a product
+    # that always leaves it alone
+    n, m = 32769, 512
+    P = torch.zeros(n, ok.packed_words(m, 4), device=DEV, dtype=torch.int32)
+    S, Z = torch.ones(n, 1, device=DEV), torch.zeros(n, 1, device=DEV)
+    size = int(ok.library().ojbkq_dequant_matmul_workspace_bytes(n, m))
+    for T, allocates in ((1, False), (32, False), (33, True)):
+        X = torch.ones(m, T, device=DEV).half()
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        ok.dequant_matmul(P, S, Z, m, 4, 0, X)
+        grown = torch.cuda.max_memory_allocated() - before
+        assert (grown >= size) == allocates, (T, grown, size)
