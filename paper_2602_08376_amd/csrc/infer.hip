@@ -879,7 +879,13 @@ hipError_t launch_dequant_matmul(const uint32_t* P, const float* S, const float*
   // unless the rows are short: n = 128256, T = 1: 192 / 657, T = 32: 192 / 617;
   // n = 131072, m = 512, T = 16: 56 / 66, with 8 bits 71 / 70; m = 256: 52 / 45.
   // (Codes of several layers in turn, so that they come from memory.)
-  if ((n + 63) / 64 * ((T + 63) / 64) <= 512 || (T <= 32 && m >= 512))
+  // A narrow layer's codes are dequantized again for every 64 tokens; from
+  // 2048 tokens on that is only worth a workgroup per CU where W_hat could be
+  // formed once (n = 256, m = 4096, T = 4096 and 8192: 8 bits 60 / 59 and 118 /
+  // 59, 4 bits 39 / 59 and 74 / 59; against dequantizing in the tiles two
+  // remain right: T = 8192: 118 / 145 and 74 / 109).
+  const int64_t blocks = (n + 63) / 64 * ((T + 63) / 64);
+  if (blocks <= (workspace && T >= 2048 ? 256 : 512) || (T <= 32 && m >= 512))
     return launch_dequant_few(a, bits, stream);
   if (workspace) {
     // W_hat once, then the product reads it instead of dequantizing every tile

@@ -97,7 +97,9 @@ def test_product_at_the_edges_of_its_kernels(n, m, T, bits, group, ld, permuted)
 
 @pytest.mark.parametrize("n,m,T,one_pass", [(32769, 512, 1, True), (32769, 512, 32, True),
                                             (32769, 512, 33, False), (32769, 504, 32, False),
-                                            (4096, 512, 100, True)])
+                                            (4096, 512, 100, True), (256, 512, 4096, True),
+                                            (256, 512, 4097, False), (600, 512, 2047, True),
+                                            (600, 512, 2048, False)])
 def test_few_tokens_leave_the_workspace(n, m, T, one_pass):
     g = torch.Generator(device=DEV).manual_seed(n + T)
     P = torch.randint(0, 2 ** 31 - 1, (n, ok.packed_words(m, 4)), generator=g, device=DEV,
@@ -110,6 +112,13 @@ def test_few_tokens_leave_the_workspace(n, m, T, one_pass):
     Y = ok.dequant_matmul(P, S, Z, m, 4, 0, X, workspace=ws)
     assert bool((ws == 0xAB).all()) == one_pass
     assert torch.equal(Y, ok.dequant_matmul(P, S, Z, m, 4, 0, X))
+    # the other form: the same sums, in another order where only this one
+    # forms W_hat (m fp16 products in float32 each)
+    other = ok.dequant_matmul(P, S, Z, m, 4, 0, X, workspace=False)
+    codes = (P.view(n, -1, 1) >> torch.arange(0, 32, 4, device=DEV)).bitwise_and(15).view(n, m)
+    W = (S * (codes - Z)).half().abs().double()
+    bound = 2 * m * 2.0 ** -24 * (W @ X.abs().double())
+    assert bool(((Y - other).abs() <= bound).all())
 
 
 def test_few_tokens_allocate_no_workspace():
