@@ -38,7 +38,7 @@ PEAK_F64_MFMA_TFLOPS = 78.6     # MI355X dense fp64 matrix peak
 PEAK_I8_MFMA_TOPS = 5000.0      # MI355X dense int8 matrix peak (5.0 POP/s)
 PEAK_HBM_GBS = 8000.0
 # int8 digit products per token and entry of the Gram and of the cross term (gram_i8.hip)
-I8_GRAM_PRODUCTS, I8_CROSS_PRODUCTS = 11, 10
+I8_DIGIT_PRODUCTS = 13
 
 
 def act_order_arg(args):
@@ -603,8 +603,8 @@ def main():
     # the int8 digit products that carry it, per token: over the Gram's lower
     # triangle m (m + 1) / 2 and (unless projected) the m^2 cross-term
     # entries, 2 operations per multiply-add
-    i8_ops = 2.0 * Tc * (I8_GRAM_PRODUCTS * m * (m + 1) / 2 +
-                         (0.0 if projected else I8_CROSS_PRODUCTS * float(m) * m))
+    i8_ops = 2.0 * Tc * I8_DIGIT_PRODUCTS * (m * (m + 1) / 2 +
+                                             (0.0 if projected else float(m) * m))
     i8_achieved = i8_ops / (gc_avg * 1e-3) / 1e12
     paths = cfg.n * (cfg.K + 1) * len(cfg.mus)
     dec_flops = float(m) * m * paths     # m^2 per candidate path (the strict triangle, 2 FLOP/MAC)

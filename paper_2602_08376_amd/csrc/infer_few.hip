@@ -63,8 +63,9 @@ struct Codes32 {
 // and read by gfx950's transposing LDS read.  The next chunk's codes, scales
 // and tokens are loaded while this one's products run.
 // 4-bit codes, m = 4096: n = 4096, T = 1: 9 us (the code's bytes at the copy
-// rate of 4.8 TB/s: 2 us; latency does the rest); n = 14336, T = 24: 25 us
-// (7 us).  With W_hat formed first and 256 x 256 tiles: 162 and 242 us.
+// rate of 4.8 TB/s: 2 us; latency does the rest); n = 14336, T = 24: 24 us with
+// the same codes again, 27 with those of forty layers in turn, from memory
+// (7 us).  With W_hat formed first and 256 x 256 tiles: 162, 242 and 248 us.
 template <int BITS, int RB, int NB>
 __global__ __launch_bounds__(512) void dequant_few_kernel(DqArgs a) {
   constexpr int kChunk = 128, kTok = 16 * NB;
